@@ -45,11 +45,36 @@ struct LayerPlan {
     size_t ffn_t;        // persistent sweep: W1 | W2 in its streaming order (DG4_FFN)
     size_t park;         // persistent sweep: rows parked between the two tiles of a pair (DG4_FFN)
     size_t bias_all;     // [n_layers][heads, 4] float: the relation biases of every layer, contiguous
-    size_t flags;        // [n] uint32 "rows published"
+    size_t flags;        // [n] uint32 "rows published" (heads spread over compute units: [heads, n])
+    size_t sync, exchange;       // heads spread over compute units: counters and mailboxes, words in flight between the slices
+    size_t exchange_bytes;
     size_t ctrl;         // abort word, ticket counter, phase timers
     size_t total;
     int64_t max_rows;
 };
+
+// Whether sweeps of this graph and configuration run with the heads of a tile spread over compute units. A
+// matter of the graph and the configuration alone, so that sweeps over part of the levels and other schedules of
+// the same graph give the same bits.
+// The line lies where a level fills the groups, 16 gates each (1024 gates at hidden 128, 512 at 256): below it the
+// sweep is bound by the chain from level to level, which spreading a tile shortens; above it by throughput, and
+// handing whole tiles to compute units wastes less. Measured, time of the other path over this one, against gates
+// per level. fp32 / 128, two hops: 1.33 at 217, 1.35 at 732, 0.94 at 1172 (four layers 1.34, 1.30, 1.01; with
+// feed-forward 1.38, 1.20, 0.92); bf16 / 256, four layers: 1.48 at 217, 1.49 at 387, 0.92 at 732; three hops 1.29,
+// 1.31, 0.77. Cones of six hops and more are bound by the gathers, of which this kernel makes fewer from memory:
+// 1.47 at 1314 and 1.62 at 3038 (fp32 / 128), 1.11 and 1.18 (bf16 / 256), so twice the line (at five hops 1.03
+// at 1314, 1.05 at 778). Where the other path is level-by-level launches (bf16 / 128, fp32 / 256, feed-forward
+// on cones of more than three hops), four times: bf16 / 128 5.5 at 217, 2.5 at 1640, 0.79 at 6780; fp32 / 256 6.7,
+// 1.8, 0.69. One layer over two hops in bf16 / 256 without feed-forward has a kernel of its own.
+bool heads_route(const dg4_layer_cfg* c, const dg4_graph* g)
+{
+    // (without marks the nodes are copies in many shallow components: never narrow)
+    if ((c->flags & (DG4_PER_LEVEL | DG4_BOUNDED_KV)) || !g->marks) return false;
+    const bool ffn = (c->flags & DG4_FFN) != 0;
+    if (c->dtype == DG4_BF16 && c->hidden == 256 && c->n_layers == 1 && c->hops <= 2 && !ffn) return false;
+    const bool streamed = dg4_flow_supports(c->dtype, c->hidden, 8) && (!ffn || c->hops <= 3);
+    return dg4_dependency_width(g) <= (int64_t)dg4_head_groups(c->heads) * DG4_HEADS_ROWS * (!streamed ? 4 : c->hops >= 6 ? 2 : 1);
+}
 
 LayerPlan plan_layer(const dg4_layer_cfg* c, const dg4_graph* g)
 {
@@ -84,7 +109,11 @@ LayerPlan plan_layer(const dg4_layer_cfg* c, const dg4_graph* g)
     p.ffn_t = take(ffn ? 2 * d * 4 * d * es : 0);
     p.park = take(ffn ? (size_t)DG4_MAX_SWEEP_GROUPS * DG4_TILE_ROWS * d * es : 0);
     p.bias_all = take(L * (size_t)c->heads * 4 * sizeof(float));
-    p.flags = take(n * sizeof(uint32_t));
+    const bool heads = heads_route(c, g);
+    p.flags = take(n * sizeof(uint32_t) * (heads ? (size_t)c->heads : 1));
+    p.sync = take(heads ? DG4_HEADS_SYNC_BYTES : 0);
+    p.exchange_bytes = heads ? (size_t)dg4_heads_exchange_bytes(c->dtype, c->hidden, ffn) : 0;
+    p.exchange = take(p.exchange_bytes);
     p.ctrl = take(256);
     p.total = off;
     return p;
@@ -317,12 +346,89 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
     // on neighbour rows wider than 16 entries).
     const bool whole_range = level_begin == 0 && level_end == (int32_t)g->max_level + 1;
     const bool forced_levels = (cfg->flags & (DG4_PER_LEVEL | DG4_BOUNDED_KV)) != 0;
-    const bool resident = dt == DG4_BF16 && d == 256 && L == 1 && cfg->hops <= 2 && !forced_levels && (!ffn || whole_range);
-    const bool flow = !resident && !forced_levels && dg4_flow_supports(dt, d, g->ell_w) && (!ffn || g->ell_w <= 16);
+    const bool heads = heads_route(cfg, g);
+    const bool resident = !heads && dt == DG4_BF16 && d == 256 && L == 1 && cfg->hops <= 2 && !forced_levels && (!ffn || whole_range);
+    const bool flow = !heads && !resident && !forced_levels && dg4_flow_supports(dt, d, g->ell_w) && (!ffn || g->ell_w <= 16);
     // a caller that has not changed the weights since its last call with this configuration, graph
     // and workspace vouches for the packed copies that call left behind
     const bool pack = !(cfg->flags & DG4_WEIGHTS_PACKED);
     const uint32_t spin_limit = cfg->spin_limit ? cfg->spin_limit : DEFAULT_SPIN_LIMIT;
+
+    const int64_t P0 = g->level_ptr[level_begin], P1 = g->level_ptr[level_end];
+    // optional timing of the persistent kernel alone (a call that runs none leaves nothing to read back)
+    const bool timed = (cfg->flags & DG4_TIME_SWEEP) != 0 && (resident || flow || heads);
+    if ((cfg->flags & DG4_TIME_SWEEP) && !timed) {
+        SweepEvents& ev = sweep_events();
+        std::lock_guard<std::mutex> lock(ev.mu);
+        ev.armed = false;
+    }
+    auto bracket = [&](auto&& launch) -> int {
+        if (!timed) return launch();
+        SweepEvents& ev = sweep_events();
+        std::lock_guard<std::mutex> lock(ev.mu);
+        if (!ev.a && (hipEventCreate(&ev.a) != hipSuccess || hipEventCreate(&ev.b) != hipSuccess)) return (int)hipErrorUnknown;
+        if (hipEventRecord(ev.a, s) != hipSuccess) return (int)hipErrorUnknown;
+        const int rc2 = launch();
+        if (rc2 != (int)hipSuccess) return rc2;
+        if (hipEventRecord(ev.b, s) != hipSuccess) return (int)hipErrorUnknown;
+        ev.armed = true;
+        return (int)hipSuccess;
+    };
+
+    if (heads) {
+        const bool wide = g->ell_w > 16;
+        dg4_heads_args a{};
+        const int rows = dg4_heads_tile_rows(g, cfg->heads);
+        if (whole_range && !wide && !g->eq1_level_ptr.empty() && !(cfg->flags & DG4_LEVEL_ORDER)) {
+            // a caller's levelling deeper than the circuit: the dependency-driven order, its tiles (8 or 16 gates) one
+            // by one or, where a level holds more than the groups, two of 8 at a time (they never depend on each other)
+            rc = dg4_graph_ensure_pairs(g);
+            if (rc != DG4_OK) return rc;
+            a.pairs = g->pair_tile_rows <= DG4_HEADS_ROWS / 2 && rows > g->pair_tile_rows ? 1 : 0;
+            a.tiles = g->d_pair_tiles; a.tile_begin = 0; a.n_tiles = a.pairs ? g->n_pair_tiles / 2 : g->n_pair_tiles;
+            a.ell = g->d_pair_ell; a.order = g->d_pair_order;
+            a.tile_rows = DG4_HEADS_ROWS;
+        } else {
+            // level by level (the dependency-driven order measured the same: 1.31 against 1.30 ms at 104 gates per level,
+            // 5.17 against 5.14 at 470, twelve layers, and costs the host a schedule)
+            const dg4_graph::LevelTiles* lt = nullptr;
+            rc = dg4_graph_ensure_level_tiles(g, rows, &lt);
+            if (rc != DG4_OK) return rc;
+            a.tiles = lt->d_tiles; a.tile_begin = lt->level_ptr[level_begin]; a.n_tiles = lt->level_ptr[level_end] - a.tile_begin;
+            a.ell = g->d_ell_pos; a.order = g->d_order;
+            a.tile_rows = wide ? rows : DG4_HEADS_ROWS;
+        }
+        a.ell_w = g->ell_w;
+        a.pre_rows = P0; a.n_pre = (P0 + DG4_HEADS_ROWS - 1) / DG4_HEADS_ROWS;
+        a.n_rows = g->n;
+        a.x = X; a.kv = at(pl.kv); a.h_out = Hout;
+        a.wqkv_packed = at(pl.wqkv[0]); a.wo_packed = at(pl.wo[0]);
+        a.w_layer_stride = L > 1 ? (int64_t)(pl.wqkv[1] - pl.wqkv[0]) : 0;
+        if (ffn) {
+            a.ffn = 1; a.w1_packed = at(pl.w1[0]); a.w2_packed = at(pl.w2[0]);
+            a.ffn_layer_stride = L > 1 ? (int64_t)(pl.w1[1] - pl.w1[0]) : 0;
+        }
+        a.rel_bias = (const float*)at(pl.bias_all);
+        a.flags = (uint32_t*)at(pl.flags); a.sync = (uint32_t*)at(pl.sync); a.exchange = (uint64_t*)at(pl.exchange);
+        a.ctrl = (uint32_t*)at(pl.ctrl);
+        a.n_layers = L; a.ln_eps = cfg->ln_eps; a.epilogue = epi ? 1 : 0;
+        a.spin_limit = spin_limit;
+        a.prof = (cfg->flags & DG4_PROFILE) ? (uint64_t*)((char*)at(pl.ctrl) + 64) : nullptr;
+        if (pack) {
+            dg4_heads_pack_args k{};
+            k.hidden = d; k.n_layers = L; k.ffn = a.ffn;
+            for (int l = 0; l < L; ++l) {
+                k.wqkv[l] = W[WS * l]; k.wo[l] = W[WS * l + 1]; k.bias[l] = (const float*)W[WS * l + 2];
+                if (ffn) { k.w1[l] = W[WS * l + 3]; k.w2[l] = W[WS * l + 4]; }
+            }
+            k.wqkv_packed = at(pl.wqkv[0]); k.wo_packed = at(pl.wo[0]); k.w_layer_stride = a.w_layer_stride;
+            if (ffn) { k.w1_packed = at(pl.w1[0]); k.w2_packed = at(pl.w2[0]); k.ffn_layer_stride = a.ffn_layer_stride; }
+            k.bias_all = (float*)at(pl.bias_all);
+            HIPCHK(dg4_launch_heads_pack(dt, k, s));
+        }
+        HIPCHK(bracket([&]() { return dg4_launch_heads(dt, d, a, (int64_t)pl.exchange_bytes, s); }));
+        return DG4_OK;
+    }
 
     if (pack) {
         for (int l = 0; l < L; ++l) {
@@ -351,8 +457,6 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
             }
         }
     }
-    const int64_t P0 = g->level_ptr[level_begin], P1 = g->level_ptr[level_end];
-
     auto kv_project = [&](const void* rows, int64_t stride, const int32_t* gather, int64_t r0, int64_t r1) -> int {
         dg4_gemm_args a{};
         a.a = rows; a.a_stride = stride; a.a_gather = gather;
@@ -369,26 +473,6 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
     // K/V of gates finished before this call (resume): from the caller's H (the persistent kernel for
     // every shape does that itself, with its own arithmetic)
     if (P0 > 0 && !bounded && !flow) HIPCHK(kv_project(Hout, d, g->d_order, 0, P0));
-
-    // optional timing of the persistent kernel alone (a call that runs none leaves nothing to read back)
-    const bool timed = (cfg->flags & DG4_TIME_SWEEP) != 0 && (resident || flow);
-    if ((cfg->flags & DG4_TIME_SWEEP) && !timed) {
-        SweepEvents& ev = sweep_events();
-        std::lock_guard<std::mutex> lock(ev.mu);
-        ev.armed = false;
-    }
-    auto bracket = [&](auto&& launch) -> int {
-        if (!timed) return launch();
-        SweepEvents& ev = sweep_events();
-        std::lock_guard<std::mutex> lock(ev.mu);
-        if (!ev.a && (hipEventCreate(&ev.a) != hipSuccess || hipEventCreate(&ev.b) != hipSuccess)) return (int)hipErrorUnknown;
-        if (hipEventRecord(ev.a, s) != hipSuccess) return (int)hipErrorUnknown;
-        const int rc2 = launch();
-        if (rc2 != (int)hipSuccess) return rc2;
-        if (hipEventRecord(ev.b, s) != hipSuccess) return (int)hipErrorUnknown;
-        ev.armed = true;
-        return (int)hipSuccess;
-    };
 
     // One persistent dataflow kernel for the whole range of levels (with the feed-forward sub-block:
     // whole-graph sweeps only, partial ones run level by level)

@@ -744,6 +744,7 @@ int dg4_graph_ensure_pairs(dg4_graph* g)
         if (!tiles.empty() && hipMemcpy(d_tiles, tiles.data(), tiles.size() * sizeof(uint2), hipMemcpyHostToDevice) != hipSuccess) return fail(DG4_EHIP);
         g->d_pair_ell = d_ell; g->d_pair_order = d_order; g->d_pair_tiles = d_tiles;
         g->n_pair_tiles = (int64_t)tiles.size();
+        for (const uint2& t : tiles) g->pair_tile_rows = std::max(g->pair_tile_rows, (int)t.y);
     } catch (const std::bad_alloc&) {
         return DG4_ENOMEM;
     }
@@ -753,6 +754,38 @@ int dg4_graph_ensure_pairs(dg4_graph* g)
 // Device tables: fixed-width packed rows, once by node id (for calls whose
 // tensors are indexed by id) and once by position in the (level, id) order
 // (for the sweep, whose internal buffers are level sorted).
+// Runs of at most `rows` positions inside a level. The caller holds g->mu.
+static int level_tiles(dg4_graph* g, int rows, const dg4_graph::LevelTiles** out)
+{
+    const int slot = rows == 2 ? 0 : rows == 4 ? 1 : rows == 8 ? 2 : rows == 16 ? 3 : -1;
+    if (slot < 0) return DG4_EINVAL;
+    dg4_graph::LevelTiles& lt = g->level_tiles[slot];
+    if (!lt.d_tiles) {
+        try {
+            std::vector<uint2> tiles;
+            std::vector<int64_t> ptr((size_t)g->max_level + 2, 0);
+            for (int32_t l = 0; l <= g->max_level; ++l) {
+                ptr[l] = (int64_t)tiles.size();
+                for (int64_t p0 = g->level_ptr[l]; p0 < g->level_ptr[l + 1]; p0 += rows)
+                    tiles.push_back(make_uint2((uint32_t)p0, (uint32_t)std::min<int64_t>(rows, g->level_ptr[l + 1] - p0)));
+            }
+            ptr[(size_t)g->max_level + 1] = (int64_t)tiles.size();
+            uint2* d = nullptr;
+            if (hipMalloc((void**)&d, std::max<size_t>(tiles.size(), 1) * sizeof(uint2)) != hipSuccess) return DG4_ENOMEM;
+            if (!tiles.empty() && hipMemcpy(d, tiles.data(), tiles.size() * sizeof(uint2), hipMemcpyHostToDevice) != hipSuccess) {
+                (void)hipFree(d);
+                return DG4_EHIP;
+            }
+            lt.level_ptr.swap(ptr);
+            lt.d_tiles = d;
+        } catch (const std::bad_alloc&) {
+            return DG4_ENOMEM;
+        }
+    }
+    if (out) *out = &lt;
+    return DG4_OK;
+}
+
 int dg4_graph_ensure_device(dg4_graph* g)
 {
     std::lock_guard<std::mutex> lock(g->mu);
@@ -927,6 +960,10 @@ int dg4_graph_ensure_device(dg4_graph* g)
     } catch (const std::bad_alloc&) {
         return DG4_ENOMEM;
     }
+    // tiles for the kernel that spreads heads over compute units, both numbers of heads (now, so that a sweep after
+    // dg4_graph_upload allocates nothing; if it fails here, that sweep tries again); wide circuits never take it
+    if (dg4_dependency_width(g) <= 4 * DG4_HEADS_ROWS * dg4_head_groups(4))
+        for (int heads : {4, 8}) (void)level_tiles(g, dg4_heads_tile_rows(g, heads), nullptr);
     g->ell_w = w; g->device = dev; g->on_device = true;
     return DG4_OK;
 }
@@ -961,6 +998,13 @@ int dg4_graph_ensure_wide_tiles(dg4_graph* g)
         return DG4_ENOMEM;
     }
     return DG4_OK;
+}
+
+int dg4_graph_ensure_level_tiles(dg4_graph* g, int rows, const dg4_graph::LevelTiles** out)
+{
+    std::lock_guard<std::mutex> lock(g->mu);
+    if (!g->on_device) return DG4_EINVAL;
+    return level_tiles(g, rows, out);
 }
 
 // Device tables of the (Eq. 1 level, id) order, see dg4_graph::eq1_level_ptr.
@@ -1106,6 +1150,8 @@ extern "C" void dg4_graph_free(dg4_graph* g)
     if (g->d_pair_ell) (void)hipFree(g->d_pair_ell);
     if (g->d_pair_order) (void)hipFree(g->d_pair_order);
     if (g->d_pair_tiles) (void)hipFree(g->d_pair_tiles);
+    for (const dg4_graph::LevelTiles& lt : g->level_tiles)
+        if (lt.d_tiles) (void)hipFree(lt.d_tiles);
     if (g->d_order_eq1) (void)hipFree(g->d_order_eq1);
     if (g->d_ell_eq1) (void)hipFree(g->d_ell_eq1);
     delete g;

@@ -21,6 +21,9 @@
 #define DG4_SCHED_TILES_PER_LEVEL 320
 #define DG4_MAX_LAYERS 16        // the paper stacks 12 (Section 4.1)
 #define DG4_TILE_ROWS 16          // gates per tile of the persistent sweep
+#define DG4_HEADS_ROWS 16         // most gates of a tile of the kernel that spreads heads over compute units
+#define DG4_HEADS_GROUPS 64       // most groups of workgroups (one workgroup per head) it runs
+#define DG4_HEADS_SYNC_BYTES 16384 // its counters and mailboxes
 #define DG4_MAX_SWEEP_GROUPS 1024 // most workgroups the persistent sweep is launched with (one per compute unit)
 
 struct dg4_graph {
@@ -68,6 +71,9 @@ struct dg4_graph {
     int wide_tile_rows = 0;
     std::vector<int64_t> level_tilew_ptr;
     uint2* d_tilesw = nullptr;
+    // runs of at most 2, 4, 8, 16 positions inside one level (the kernel that spreads heads over compute units), on first use
+    struct LevelTiles { std::vector<int64_t> level_ptr; uint2* d_tiles = nullptr; };
+    LevelTiles level_tiles[4];
     // A second processing order for sweeps over ALL levels: tiles filled by list scheduling over
     // the real dependencies (a gate goes as early as its sources allow, sources long finished
     // first), not level by level. Host copy (node ids in processing order, first position of
@@ -94,7 +100,27 @@ struct dg4_graph {
     int32_t* d_pair_order = nullptr;
     uint2* d_pair_tiles = nullptr;
     int64_t n_pair_tiles = 0;
+    int pair_tile_rows = 0;          // gates of its largest tile
 };
+
+// Gates per level of the dependencies a whole sweep follows
+inline int64_t dg4_dependency_width(const dg4_graph* g)
+{
+    const int64_t depth = g->eq1_level_ptr.empty() ? (int64_t)g->max_level + 1 : (int64_t)g->eq1_level_ptr.size() - 1;
+    return g->n / (depth > 0 ? depth : 1);
+}
+// Groups of workgroups, one workgroup per head, that 256 compute units hold
+inline int dg4_head_groups(int heads) { return 256 / heads; }
+// Gates per tile of a level where the heads are spread over compute units: one round of tiles over the groups, up
+// to a quarter more (levels overlap a little: 262 gates over 32 groups 12.4 ms with tiles of 8, 15.9 with 16; 236
+// over 64 groups 7.8 with 4, 9.8 with 8)
+inline int dg4_heads_tile_rows(const dg4_graph* g, int heads)
+{
+    const int64_t width = dg4_dependency_width(g);
+    int rows = 2;
+    while (rows < DG4_HEADS_ROWS && 4 * width > 5 * (int64_t)dg4_head_groups(heads) * rows) rows *= 2;
+    return rows;
+}
 
 // dg4_qkv_proj in two parts (dg4_api.cpp): the argument checks that do not concern the workspace, and
 // the launches, which allocate nothing; shared with dg4_qkv_proj_static.
@@ -110,6 +136,7 @@ int dg4_pair_schedule(dg4_graph* g);   // caller holds g->mu
 int dg4_graph_ensure_frontier(dg4_graph* g);           // after dg4_graph_ensure_device
 int dg4_graph_ensure_struct(dg4_graph* g);
 int dg4_graph_ensure_pairs(dg4_graph* g);              // after dg4_graph_ensure_device
+int dg4_graph_ensure_level_tiles(dg4_graph* g, int rows, const dg4_graph::LevelTiles** out);   // rows 2, 4, 8 or 16; after dg4_graph_ensure_device
 int dg4_graph_ensure_wide_tiles(dg4_graph* g);         // after dg4_graph_ensure_device; graphs with rows wider than 16 entries
 int dg4_graph_ensure_eq1(dg4_graph* g);                // after dg4_graph_ensure_device; needs eq1_level_ptr
 
@@ -234,6 +261,46 @@ bool dg4_flow_supports(int dtype, int hidden, int ell_w);
 int dg4_launch_pack_wa(int dtype, int hidden, const void* w, int ld, int col0, int n_cols, void* packed, hipStream_t s);
 int dg4_launch_flow(int dtype, int hidden, const dg4_flow_args& a, hipStream_t s);
 
+// ---- persistent dataflow sweep with the heads of a tile spread over compute units (dg4_heads.hip): circuits with few
+// gates per level, every hidden size and type, rows of any width, any number of layers ----
+struct dg4_heads_args {
+    const uint2* tiles; int64_t tile_begin; int64_t n_tiles;   // as dg4_flow_args; at most DG4_HEADS_ROWS gates per tile
+    int pairs;
+    int64_t n_pre; int64_t pre_rows;       // resumed sweeps, DG4_HEADS_ROWS positions per extra tile
+    const uint32_t* ell; int ell_w;        // neighbour rows by position
+    int tile_rows;                         // rows wider than 16 entries: most gates of a tile (2, 4, 8 or 16); else DG4_HEADS_ROWS
+    int lanes_log2;                        // log2 of 512 / tile_rows (set by the launcher)
+    int64_t n_rows;                        // gates of the graph
+    const int32_t* order;                  // position -> node id
+    const void* x;                         // [n, d] by node id
+    void* kv;                              // [layers][heads][n][K 32 | V 32] by position
+    void* h_out;                           // [n, d] by node id
+    const void* wqkv_packed; const void* wo_packed; int64_t w_layer_stride;    // dg4_launch_heads_pack order; bytes between layers
+    int ffn;
+    const void* w1_packed; const void* w2_packed; int64_t ffn_layer_stride;
+    const float* rel_bias;                 // [layers][heads, 4]
+    uint32_t* flags;                       // [heads][n] by position: 1 = the head's rows are in the store
+    uint32_t* sync;                        // DG4_HEADS_SYNC_BYTES: ticket and check-in counters, mailboxes
+    uint64_t* exchange;                    // dg4_heads_exchange_bytes
+    uint32_t* ctrl;                        // [1] abort word
+    uint64_t* prof;                        // nullable: phase timers (10 ns ticks, summed over workgroups)
+    int n_layers;
+    float ln_eps; int epilogue;
+    uint32_t spin_limit;
+};
+struct dg4_heads_pack_args {
+    int hidden, n_layers, ffn;
+    const void* wqkv[DG4_MAX_LAYERS]; const void* wo[DG4_MAX_LAYERS]; const float* bias[DG4_MAX_LAYERS];
+    const void* w1[DG4_MAX_LAYERS]; const void* w2[DG4_MAX_LAYERS];
+    void* wqkv_packed; void* wo_packed; int64_t w_layer_stride;
+    void* w1_packed; void* w2_packed; int64_t ffn_layer_stride;
+    float* bias_all;
+};
+int64_t dg4_heads_exchange_bytes(int dtype, int hidden, bool ffn);
+int dg4_launch_heads_pack(int dtype, const dg4_heads_pack_args& a, hipStream_t s);
+// clears flags, tickets, control words and the exchange buffer, then sweeps
+int dg4_launch_heads(int dtype, int hidden, const dg4_heads_args& a, int64_t exchange_bytes, hipStream_t s);
+
 // ---- bulk projection on the matrix cores (dg4_sweep.hip): bf16, hidden 256 ----
 struct dg4_bulk_args {
     const uint16_t* src;                   // [*, 256] input rows
@@ -256,4 +323,6 @@ DG4_CHECK_KERNEL_ARGS(dg4_ffn_args);
 DG4_CHECK_KERNEL_ARGS(dg4_sweep_args);
 DG4_CHECK_KERNEL_ARGS(dg4_flow_args);
 DG4_CHECK_KERNEL_ARGS(dg4_bulk_args);
+DG4_CHECK_KERNEL_ARGS(dg4_heads_args);
+DG4_CHECK_KERNEL_ARGS(dg4_heads_pack_args);
 #undef DG4_CHECK_KERNEL_ARGS

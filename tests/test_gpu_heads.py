@@ -1,0 +1,112 @@
+"""The persistent kernel that spreads the heads of a tile over compute units (circuits with few gates per level):
+every hidden size and type, rows of every width class, every tile size, against the oracle and, bit for bit,
+against itself under other schedules and cuts. The level-by-level path (other kernels) is the second opinion."""
+import numpy as np
+import pytest
+import torch
+
+import dg4_synth as synth
+import oracle
+import paper_2502_01681_amd as dg4
+from gpu_utils import TOL, cfg_of, device_weights, row_rel_err, tdtype, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def make(n_and, window, hidden, dtype, hops, layers, n_pi=40):
+    return synth.make(synth.Config("heads", 77, n_pi, n_and, window, 1.0, 0, hidden, hidden // 32, hops, layers, dtype))
+
+
+def run(w, cfg, g, ffn=None, level_begin=0, level_end=None, H0=None):
+    X, W = to_dev(w.x, cfg.dtype), device_weights(w, cfg.dtype)
+    if ffn is not None:
+        W = [lw + (to_dev(ffn[0][l], cfg.dtype), to_dev(ffn[1][l], cfg.dtype)) for l, lw in enumerate(W)]
+    H = torch.full((w.cfg.n_nodes, cfg.hidden), float("nan"), dtype=tdtype(cfg.dtype), device="cuda") if H0 is None else H0
+    ws = torch.empty(dg4.dg4_layer_workspace_bytes(cfg, g), dtype=torch.uint8, device="cuda")
+    ws.fill_(0xFF)                          # NaN patterns: nothing may be read before it is written
+    dg4.dg4_layer_fwd(cfg, g, X, W, H, level_begin, level_end, workspace=ws)
+    torch.cuda.synchronize()
+    dg4.dg4_layer_status(cfg, g, ws)
+    return H
+
+
+@pytest.mark.parametrize("hidden,dtype", [(128, "f32"), (128, "bf16"), (256, "f32"), (256, "bf16")])
+@pytest.mark.parametrize("n_and,window,hops,layers,ffn", [
+    (3, 2, 1, 2, False),                    # fewer gates than a tile, fewer tiles than groups
+    (700, 60, 2, 2, False), (700, 60, 3, 1, False),
+    (2_500, 2_400, 2, 2, False),            # a few hundred gates per level: two tiles of 8 at a time
+    (600, 60, 2, 2, True),
+    (500, 20, 5, 2, False),                 # wide rows, tiles of two gates (16 lane groups and more per gate)
+    (1_500, 900, 5, 1, False),              # tiles of four and eight
+    (4_000, 3_900, 4, 2, False),            # tiles of sixteen
+    (900, 300, 6, 2, True),
+])
+def test_heads_kernel_against_oracle(hidden, dtype, n_and, window, hops, layers, ffn):
+    print(f"heads kernel {dtype} {hidden} n_and={n_and} window={window} hops={hops} layers={layers} ffn={ffn}", flush=True)
+    w = make(n_and, window, hidden, dtype, hops, layers)
+    c = w.cfg
+    fw = synth.ffn_weights(c) if ffn else None
+    g = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops)
+    cfg = cfg_of(c, ffn=ffn)
+    H = run(w, cfg, g, fw)
+    assert not torch.isnan(H.float()).any()
+    og = oracle.build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops)
+    kw = dict(w1=fw[0], w2=fw[1]) if ffn else {}
+    ref = oracle.layer_fwd(og, w.x, w.wqkv, w.wo, w.rel_bias, c.heads, store=dtype, **kw)
+    err = row_rel_err(to_np(H), ref).max()
+    print(f"  {g.n_levels} levels, max rel err {err:.3e}", flush=True)
+    assert err <= TOL[dtype]
+    # other kernels, another summation order: each within TOL of the oracle
+    assert row_rel_err(to_np(H), to_np(run(w, cfg_of(c, ffn=ffn, per_level=True), g, fw)).astype(np.float64)).max() <= 2 * TOL[dtype]
+    assert torch.equal(H, run(w, cfg_of(c, ffn=ffn, level_order=True), g, fw))
+    mid = g.n_levels // 2
+    assert torch.equal(H, run(w, cfg, g, fw, mid, None, H0=run(w, cfg, g, fw, 0, mid)))
+
+
+@pytest.mark.parametrize("hidden,dtype", [(128, "bf16"), (256, "f32")])
+def test_heads_kernel_without_epilogue_and_with_masking_biases(hidden, dtype):
+    # relation biases of -inf and of the type's lowest value take entries out of the softmax; the gate itself stays
+    w = make(600, 50, hidden, dtype, 3, 1)
+    c = w.cfg
+    for code, value in ((3, -np.inf), (1, np.finfo(np.float32).min)):
+        w.rel_bias[0][:, code] = value
+    g = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, 3)
+    og = oracle.build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, 3)
+    for epilogue in (True, False):
+        H = run(w, cfg_of(c, epilogue=epilogue), g)
+        ref = oracle.layer_fwd(og, w.x, w.wqkv, w.wo, w.rel_bias, c.heads, store=dtype, epilogue=epilogue)
+        assert row_rel_err(to_np(H), ref).max() <= TOL[dtype], epilogue
+
+
+def test_heads_kernel_bounded_wait_two_streams_and_packed_weights():
+    # A spin limit of one may end the sweep early: it returns, says so, and the same workspace then serves a
+    # normal sweep. Two sweeps at once on two streams (more workgroups than compute units): the same bits.
+    w = make(2_000, 200, 128, "f32", 2, 3)
+    c = w.cfg
+    g = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, 2)
+    cfg = cfg_of(c)
+    H = run(w, cfg, g)
+    X, W = to_dev(w.x, c.dtype), device_weights(w, c.dtype)
+    out = torch.full_like(H, float("nan"))
+    ws = torch.empty(dg4.dg4_layer_workspace_bytes(cfg, g), dtype=torch.uint8, device="cuda")
+    print("heads kernel: spin limit 1", flush=True)
+    dg4.dg4_layer_fwd(cfg_of(c, spin_limit=1), g, X, W, out, workspace=ws)
+    torch.cuda.synchronize()
+    assert dg4.dg4_layer_status(cfg, g, ws, check=False) in (0, -10)
+    for again in (cfg, cfg_of(c, weights_packed=True)):
+        out.fill_(float("nan"))
+        dg4.dg4_layer_fwd(again, g, X, W, out, workspace=ws)
+        torch.cuda.synchronize()
+        dg4.dg4_layer_status(cfg, g, ws)
+        assert torch.equal(out, H)
+    print("heads kernel: two streams", flush=True)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    both = [(torch.full_like(H, float("nan")), torch.empty_like(ws)) for _ in streams]
+    torch.cuda.synchronize()
+    for s, (o, k) in zip(streams, both):
+        with torch.cuda.stream(s):
+            dg4.dg4_layer_fwd(cfg, g, X, W, o, workspace=k)
+    torch.cuda.synchronize()
+    for o, k in both:
+        dg4.dg4_layer_status(cfg, g, k)
+        assert torch.equal(o, H)
