@@ -756,46 +756,62 @@ __global__ __launch_bounds__(256) void ffn_kernel(dg4_ffn_args p)
     }
 }
 
-// ------------------------------------------------- feed-forward, many rows at once (bf16, d = 256)
+// ------------------------------------------------- feed-forward, many rows at once (dg4_ffn_fwd)
 //
-// dg4_ffn_fwd over a whole matrix is bound by how often the megabyte of W1 | W2 has to come from
-// the L2 cache: ffn_kernel above reads it once per 32 rows. Here a workgroup takes 64 rows, keeps
-// them in LDS, and streams the weights once for all of them: one contiguous stream per wave, in
-// four passes of 256 hidden units. Per pass a wave forms the activations of its 64 hidden units
-// for all 64 rows (transposed, W1 piece as the A operand), rectifies and writes them to LDS,
-// and after a barrier adds the pass's part of ITS 64 output columns for all rows (the output
-// accumulators, 64 registers, stay put over the passes). Residual + LayerNorm from registers with
-// the row sums completed through LDS; the result leaves through LDS as whole 16-byte pieces.
-// Two workgroups share a compute unit (70 KB of LDS and at most 256 registers each), so that one
-// computes while the other waits at a barrier or for its rows: measured 1.18 ms for 1M rows, against
-// 1.32 ms with 96 rows and one workgroup per compute unit (a third less weight traffic, no overlap).
-constexpr int FB_ROWS = 64, FB_RT = 2, FB_STRIDE = 264, FB_PASSES = 4, FB_FRAGS = 64, FB_RING = 8;
-constexpr int FB_SMEM = 2 * FB_ROWS * FB_STRIDE * 2 + 2 * 4 * FB_ROWS * 4;
+// dg4_ffn_fwd over a whole matrix in bf16 is bound by how often the weights have to come from the L2
+// cache, in fp32 by the matrix cores: ffn_kernel above reads the weights once per 32 rows, straight into each
+// product, and its output accumulators and operands (128 registers each at fp32 / 256) leave one wave
+// per SIMD to wait for them. Here a workgroup keeps its rows in LDS and streams the weights once for all of
+// them: one contiguous stream per wave through a ring of fragments, in passes of 256 hidden units. Per pass
+// a wave forms the activations of its 64 hidden units for all rows (transposed, W1 piece as the A
+// operand), rectifies and writes them to LDS, and after a barrier adds the pass's part of ITS quarter of the
+// output columns for all rows (the output accumulators stay put over the passes). Residual + LayerNorm
+// from registers with the row sums completed through LDS; the result leaves through LDS as whole 16-byte
+// pieces. Two or more workgroups share a compute unit (at most 70 KB of LDS and 256 registers each), so
+// that one computes while the other waits at a barrier or for its rows. bf16 / 256, 64 rows per workgroup:
+// 1.18 ms for 1M rows, against 1.32 ms with 96 rows and one workgroup per compute unit (a third less
+// weight traffic, no overlap). fp32 takes 32 rows: a fragment then feeds four products of 64 cycles, which
+// hides its way from the L2, and two workgroups fit. Against ffn_kernel, 61,003 rows: fp32 / 256 1534 -> 545 us
+// (117 TFLOP/s of the 153 a large matrix product reaches), fp32 / 128 243 -> 153, bf16 / 128 75 -> 28; 33 rows 202 -> 71,
+// 63 -> 23, 34 -> 16 us.
+template <typename T, int D> struct FfnBulk {
+    static constexpr int E = 16 / (int)sizeof(T);                 // elements in 16 bytes
+    static constexpr int RT = sizeof(T) == 4 ? 1 : 2;             // row tiles of 32
+    static constexpr int ROWS = 32 * RT;
+    static constexpr int PASSES = 4 * D / 256;
+    static constexpr int KC = D / (2 * E);                        // steps of the first product along a row
+    static constexpr int CT = D / 128;                            // column tiles of 32 per wave
+    static constexpr int F1 = 2 * KC, F2 = 256 / (2 * E) * CT;    // fragments per pass: first, second product
+    static constexpr int FRAGS = F1 + F2, RING = 8;
+    static constexpr int HS = D + E, US = 256 + E;                // row strides in LDS
+    static constexpr int SMEM = ROWS * (HS + US) * (int)sizeof(T) + 2 * 4 * ROWS * 4;
+    static_assert(F1 % RING == 0 && F2 % RING == 0, "whole rings");
+};
 
-// Stream order, 16-byte units: (((w*4 + pass)*64 + j)*64 + lane), lane = 32*kg + m.
-//  j < 32 : first product, hidden tile t = j/16, k-step ks = j%16:
-//           W1[16*ks + 8*kg + e][256*pass + 64*w + 32*t + m], e = 0..7
-//  j >= 32: second product, k-step ks = (j-32)/2, column tile ct = (j-32)%2:
-//           W2[256*pass + 16*ks + 8*kg + e][64*w + 32*ct + m]
-__global__ void pack_ffn_bulk_kernel(const uint16_t* w1, const uint16_t* w2, uint16_t* packed)
+// Stream order, 16-byte units: (((w*PASSES + pass)*FRAGS + j)*64 + lane), lane = 32*kg + m.
+//  j < F1 : first product, hidden tile t = j / KC, step ks = j % KC:
+//           W1[(2*ks + kg)*E + e][256*pass + 64*w + 32*t + m]
+//  j >= F1: second product, step ks = (j - F1) / CT, column tile ct = (j - F1) % CT:
+//           W2[256*pass + (2*ks + kg)*E + e][32*CT*w + 32*ct + m]
+template <typename T, int D>
+__global__ void pack_ffn_bulk_kernel(const T* w1, const T* w2, T* packed)
 {
+    typedef FfnBulk<T, D> B;
     const int64_t unit = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (unit >= 4 * FB_PASSES * FB_FRAGS * 64) return;
+    if (unit >= 4 * B::PASSES * B::FRAGS * 64) return;
     const int lane = (int)(unit & 63);
-    const int j = (int)((unit >> 6) % FB_FRAGS);
-    const int pass = (int)((unit >> 12) % FB_PASSES);
-    const int w = (int)(unit >> 14);
+    const int j = (int)((unit >> 6) % B::FRAGS);
+    const int pass = (int)((unit >> 6) / B::FRAGS % B::PASSES);
+    const int w = (int)((unit >> 6) / (B::FRAGS * B::PASSES));
     const int m = lane & 31, kg = lane >> 5;
-    if (j < 32) {
-        const int t = j >> 4, ks = j & 15;
-        const int hidden = 256 * pass + 64 * w + 32 * t + m;
+    if (j < B::F1) {
+        const int hidden = 256 * pass + 64 * w + 32 * (j / B::KC) + m;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) packed[unit * 8 + e] = w1[(int64_t)(16 * ks + 8 * kg + e) * 1024 + hidden];
+        for (int e = 0; e < B::E; ++e) packed[unit * B::E + e] = w1[(int64_t)((2 * (j % B::KC) + kg) * B::E + e) * (4 * D) + hidden];
     } else {
-        const int ks = (j - 32) >> 1, ct = (j - 32) & 1;
-        const int col = 64 * w + 32 * ct + m;
+        const int ks = (j - B::F1) / B::CT, col = 32 * B::CT * w + 32 * ((j - B::F1) % B::CT) + m;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) packed[unit * 8 + e] = w2[(int64_t)(256 * pass + 16 * ks + 8 * kg + e) * 256 + col];
+        for (int e = 0; e < B::E; ++e) packed[unit * B::E + e] = w2[(int64_t)(256 * pass + (2 * ks + kg) * B::E + e) * D + col];
     }
 }
 
@@ -807,114 +823,163 @@ __device__ __forceinline__ void lds_barrier()      // LDS traffic only: the weig
     __asm__ volatile("" ::: "memory");
 }
 
+// four consecutive elements of a row in LDS
+template <typename T> struct Quad;
+template <> struct Quad<bf16_t> {
+    __device__ static __forceinline__ void load(const bf16_t* p, float* f)
+    {
+        const uint2 v = *(const uint2*)p;
+        f[0] = bf16_lo(v.x); f[1] = bf16_hi(v.x); f[2] = bf16_lo(v.y); f[3] = bf16_hi(v.y);
+    }
+    __device__ static __forceinline__ void store(bf16_t* p, const float* f)
+    {
+        *(uint2*)p = make_uint2(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]));
+    }
+};
+template <> struct Quad<float> {
+    __device__ static __forceinline__ void load(const float* p, float* f)
+    {
+        const float4 v = *(const float4*)p;
+        f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+    }
+    __device__ static __forceinline__ void store(float* p, const float* f) { *(float4*)p = make_float4(f[0], f[1], f[2], f[3]); }
+};
+
+template <typename T, int D>
 __global__ __launch_bounds__(256, 2) void ffn_bulk_kernel(dg4_ffn_args p)
 {
+    typedef FfnBulk<T, D> B;
+    constexpr int E = B::E, RT = B::RT, KC = B::KC, CT = B::CT, RING = B::RING, PPR = D / E;
     extern __shared__ __attribute__((aligned(16))) unsigned char fb_smem[];
-    uint16_t (*sH)[FB_STRIDE] = (uint16_t (*)[FB_STRIDE])fb_smem;
-    uint16_t (*sU)[FB_STRIDE] = sH + FB_ROWS;
-    float (*sPart)[4][FB_ROWS] = (float (*)[4][FB_ROWS])(fb_smem + 2 * FB_ROWS * FB_STRIDE * 2);
+    T (*sH)[B::HS] = (T (*)[B::HS])fb_smem;
+    T (*sU)[B::US] = (T (*)[B::US])(fb_smem + B::ROWS * B::HS * sizeof(T));
+    float (*sPart)[4][B::ROWS] = (float (*)[4][B::ROWS])(fb_smem + B::ROWS * (B::HS + B::US) * sizeof(T));
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int m = lane & 31, kg = lane >> 5;
-    const int64_t r0 = p.row_begin + (int64_t)blockIdx.x * FB_ROWS;
-    const uint16_t* h = (const uint16_t*)p.h;
+    const int64_t r0 = p.row_begin + (int64_t)blockIdx.x * B::ROWS;
+    const T* h = (const T*)p.h;
 
     // the rows of this workgroup (past the end: the last row again; never stored)
 #pragma unroll
-    for (int i = 0; i < FB_ROWS * 32 / 256; ++i) {
-        const int chunk = tid + 256 * i, row = chunk >> 5, c16 = chunk & 31;
+    for (int i = 0; i < B::ROWS * PPR / 256; ++i) {
+        const int chunk = tid + 256 * i, row = chunk / PPR, c16 = chunk % PPR;
         int64_t r = r0 + row;
         if (r >= p.row_end) r = p.row_end - 1;
-        *(uint4*)&sH[row][c16 * 8] = *(const uint4*)(h + r * p.h_stride + c16 * 8);
+        *(uint4*)&sH[row][c16 * E] = *(const uint4*)(h + r * p.h_stride + c16 * E);
     }
-    const uint4* wp = (const uint4*)p.w1_packed + (int64_t)wave * (FB_PASSES * FB_FRAGS * 64) + lane;
-    uint4 ring[FB_RING];
+    const uint4* wp = (const uint4*)p.w1_packed + (int64_t)wave * (B::PASSES * B::FRAGS * 64) + lane;
+    uint4 ring[RING];
 #pragma unroll
-    for (int j = 0; j < FB_RING; ++j) ring[j] = wp[j * 64];
+    for (int j = 0; j < RING; ++j) ring[j] = wp[j * 64];
     __syncthreads();
 
-    f32x16 out[2][FB_RT];
+    // fp32: a chain of additions per d hidden units and the sum of the four chains (one chain over all 4d is 1.4
+    // times as far from 64 bits: 2.9e-7 against 2.1e-7 at 256)
+    constexpr bool SPLIT = sizeof(T) == 4;
+    f32x16 out[CT][RT], sum[SPLIT ? CT : 1][SPLIT ? RT : 1];
 #pragma unroll 1
-    for (int pass = 0; pass < FB_PASSES; ++pass) {
-        const uint4* wq = wp + (int64_t)pass * (FB_FRAGS * 64);
-        const bool more = pass + 1 < FB_PASSES;
+    for (int pass = 0; pass < B::PASSES; ++pass) {
+        const uint4* wq = wp + (int64_t)pass * (B::FRAGS * 64);
+        const bool more = pass + 1 < B::PASSES;
         if (pass) lds_barrier();                  // the previous pass's activations have been read by every wave
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            f32x16 u[FB_RT];
+            f32x16 u[RT];
             // (the rows' operands of the next step are read from LDS while this step's products run)
-            uint4 bc[FB_RT], bn[FB_RT];
+            uint4 bc[RT], bn[RT];
 #pragma unroll
-            for (int rt = 0; rt < FB_RT; ++rt) bc[rt] = *(const uint4*)&sH[32 * rt + m][8 * kg];
+            for (int rt = 0; rt < RT; ++rt) bc[rt] = *(const uint4*)&sH[32 * rt + m][E * kg];
 #pragma unroll
-            for (int ks = 0; ks < 16; ++ks) {
-                const int j = 16 * t + ks;
+            for (int ks = 0; ks < KC; ++ks) {
+                const int j = KC * t + ks;
 #pragma unroll
-                for (int rt = 0; rt < FB_RT; ++rt) bn[rt] = ks + 1 < 16 ? *(const uint4*)&sH[32 * rt + m][16 * (ks + 1) + 8 * kg] : bc[rt];
+                for (int rt = 0; rt < RT; ++rt) bn[rt] = ks + 1 < KC ? *(const uint4*)&sH[32 * rt + m][2 * E * (ks + 1) + E * kg] : bc[rt];
 #pragma unroll
-                for (int rt = 0; rt < FB_RT; ++rt) {
+                for (int rt = 0; rt < RT; ++rt) {
                     if (ks == 0) {
 #pragma unroll
                         for (int i = 0; i < 16; ++i) u[rt][i] = 0.f;
                     }
-                    Mma<bf16_t>::run(ring[j % FB_RING], bc[rt], u[rt]);
+                    Mma<T>::run(ring[j % RING], bc[rt], u[rt]);
                 }
-                ring[j % FB_RING] = wq[(j + FB_RING) * 64];
+                ring[j % RING] = wq[(j + RING) * 64];
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int rt = 0; rt < FB_RT; ++rt) bc[rt] = bn[rt];
+                for (int rt = 0; rt < RT; ++rt) bc[rt] = bn[rt];
             }
             // rectified, to LDS by row: element i of the accumulator is hidden unit 8*(i/4) + 4*kg + i%4 of the tile
 #pragma unroll
-            for (int rt = 0; rt < FB_RT; ++rt)
+            for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *(uint2*)&sU[32 * rt + m][64 * wave + 32 * t + 8 * q + 4 * kg] =
-                        make_uint2(pack_bf16x2(fmaxf(u[rt][4 * q], 0.f), fmaxf(u[rt][4 * q + 1], 0.f)),
-                                   pack_bf16x2(fmaxf(u[rt][4 * q + 2], 0.f), fmaxf(u[rt][4 * q + 3], 0.f)));
+                for (int q = 0; q < 4; ++q) {
+                    float v[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] = fmaxf(u[rt][4 * q + r], 0.f);
+                    Quad<T>::store(&sU[32 * rt + m][64 * wave + 32 * t + 8 * q + 4 * kg], v);
+                }
         }
         lds_barrier();
         {
-            uint4 bc[FB_RT], bn[FB_RT];
+            uint4 bc[RT], bn[RT];
 #pragma unroll
-            for (int rt = 0; rt < FB_RT; ++rt) bc[rt] = *(const uint4*)&sU[32 * rt + m][8 * kg];
+            for (int rt = 0; rt < RT; ++rt) bc[rt] = *(const uint4*)&sU[32 * rt + m][E * kg];
 #pragma unroll
-            for (int ks = 0; ks < 16; ++ks) {
+            for (int ks = 0; ks < B::F2 / CT; ++ks) {
 #pragma unroll
-                for (int rt = 0; rt < FB_RT; ++rt) bn[rt] = ks + 1 < 16 ? *(const uint4*)&sU[32 * rt + m][16 * (ks + 1) + 8 * kg] : bc[rt];
+                for (int rt = 0; rt < RT; ++rt) bn[rt] = ks + 1 < B::F2 / CT ? *(const uint4*)&sU[32 * rt + m][2 * E * (ks + 1) + E * kg] : bc[rt];
 #pragma unroll
-                for (int ct = 0; ct < 2; ++ct) {
-                    const int j = 32 + 2 * ks + ct;
+                for (int ct = 0; ct < CT; ++ct) {
+                    const int j = B::F1 + CT * ks + ct;
 #pragma unroll
-                    for (int rt = 0; rt < FB_RT; ++rt) {
-                        if (pass == 0 && ks == 0) {
+                    for (int rt = 0; rt < RT; ++rt) {
+                        if (SPLIT ? ks % KC == 0 : pass == 0 && ks == 0) {
 #pragma unroll
-                            for (int i = 0; i < 16; ++i) out[ct][rt][i] = 0.f;
+                            for (int i = 0; i < 16; ++i) {
+                                if constexpr (SPLIT)
+                                    if (ks > 0) sum[ct][rt][i] = pass ? sum[ct][rt][i] + out[ct][rt][i] : out[ct][rt][i];
+                                out[ct][rt][i] = 0.f;
+                            }
                         }
-                        Mma<bf16_t>::run(ring[j % FB_RING], bc[rt], out[ct][rt]);
+                        Mma<T>::run(ring[j % RING], bc[rt], out[ct][rt]);
                     }
-                    if (j + FB_RING < FB_FRAGS || more) ring[j % FB_RING] = wq[(j + FB_RING) * 64];
+                    if (j + RING < B::FRAGS || more) ring[j % RING] = wq[(j + RING) * 64];
                 }
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int rt = 0; rt < FB_RT; ++rt) bc[rt] = bn[rt];
+                for (int rt = 0; rt < RT; ++rt) bc[rt] = bn[rt];
             }
         }
+        if constexpr (SPLIT) {
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) sum[ct][rt][i] = pass || B::F2 / CT > KC ? sum[ct][rt][i] + out[ct][rt][i] : out[ct][rt][i];
+        }
+    }
+    if constexpr (SPLIT) {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) out[ct][rt] = sum[ct][rt];
     }
 
     // residual and LayerNorm (no affine, biased variance, two passes). Lane (m, kg) holds, of row
-    // 32*rt + m, the columns 64*wave + 32*ct + 8*q + 4*kg + r (accumulator element 4*q + r).
-    float mean[FB_RT];
+    // 32*rt + m, the columns 32*CT*wave + 32*ct + 8*q + 4*kg + r (accumulator element 4*q + r).
+    float mean[RT];
 #pragma unroll
-    for (int rt = 0; rt < FB_RT; ++rt) {
+    for (int rt = 0; rt < RT; ++rt) {
         float s1 = 0.f;
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct)
+        for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const uint2 hv = *(const uint2*)&sH[32 * rt + m][64 * wave + 32 * ct + 8 * q + 4 * kg];
-                out[ct][rt][4 * q] += bf16_lo(hv.x); out[ct][rt][4 * q + 1] += bf16_hi(hv.x);
-                out[ct][rt][4 * q + 2] += bf16_lo(hv.y); out[ct][rt][4 * q + 3] += bf16_hi(hv.y);
+                float hv[4];
+                Quad<T>::load(&sH[32 * rt + m][32 * CT * wave + 32 * ct + 8 * q + 4 * kg], hv);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) out[ct][rt][4 * q + r] += hv[r];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) s1 += out[ct][rt][4 * q + r];
             }
@@ -923,12 +988,12 @@ __global__ __launch_bounds__(256, 2) void ffn_bulk_kernel(dg4_ffn_args p)
     }
     __syncthreads();                              // also: every wave is done with the activations in sU
 #pragma unroll
-    for (int rt = 0; rt < FB_RT; ++rt) {
+    for (int rt = 0; rt < RT; ++rt) {
         const int row = 32 * rt + m;
-        mean[rt] = (sPart[0][0][row] + sPart[0][1][row] + sPart[0][2][row] + sPart[0][3][row]) * (1.0f / 256);
+        mean[rt] = (sPart[0][0][row] + sPart[0][1][row] + sPart[0][2][row] + sPart[0][3][row]) * (1.0f / D);
         float s2 = 0.f;
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct)
+        for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
             for (int i = 0; i < 16; ++i) { const float d = out[ct][rt][i] - mean[rt]; s2 = fmaf(d, d, s2); }
         s2 += __shfl_xor(s2, 32);
@@ -936,32 +1001,53 @@ __global__ __launch_bounds__(256, 2) void ffn_bulk_kernel(dg4_ffn_args p)
     }
     __syncthreads();
 #pragma unroll
-    for (int rt = 0; rt < FB_RT; ++rt) {
+    for (int rt = 0; rt < RT; ++rt) {
         const int row = 32 * rt + m;
-        const float rstd = rsqrtf((sPart[1][0][row] + sPart[1][1][row] + sPart[1][2][row] + sPart[1][3][row]) * (1.0f / 256) + p.ln_eps);
+        const float rstd = rsqrtf((sPart[1][0][row] + sPart[1][1][row] + sPart[1][2][row] + sPart[1][3][row]) * (1.0f / D) + p.ln_eps);
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct)
+        for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 float y[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) y[r] = (out[ct][rt][4 * q + r] - mean[rt]) * rstd;
-                *(uint2*)&sU[row][64 * wave + 32 * ct + 8 * q + 4 * kg] = make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+                Quad<T>::store(&sU[row][32 * CT * wave + 32 * ct + 8 * q + 4 * kg], y);
             }
     }
     __syncthreads();
-    uint16_t* o = (uint16_t*)p.out;
-    uint16_t* o2 = (uint16_t*)p.out2;
+    T* o = (T*)p.out;
+    T* o2 = (T*)p.out2;
 #pragma unroll
-    for (int i = 0; i < FB_ROWS * 32 / 256; ++i) {
-        const int chunk = tid + 256 * i, row = chunk >> 5, c16 = chunk & 31;
+    for (int i = 0; i < B::ROWS * PPR / 256; ++i) {
+        const int chunk = tid + 256 * i, row = chunk / PPR, c16 = chunk % PPR;
         const int64_t r = r0 + row;
         if (r >= p.row_end) continue;
-        const uint4 v = *(const uint4*)&sU[row][c16 * 8];
+        const uint4 v = *(const uint4*)&sU[row][c16 * E];
         const int64_t orr = p.out_scatter ? (int64_t)p.out_scatter[r] : r;
-        *(uint4*)(o + orr * p.out_stride + c16 * 8) = v;
-        if (o2) *(uint4*)(o2 + r * p.out2_stride + c16 * 8) = v;
+        *(uint4*)(o + orr * p.out_stride + c16 * E) = v;
+        if (o2) *(uint4*)(o2 + r * p.out2_stride + c16 * E) = v;
     }
+}
+
+template <typename T, int D>
+int launch_pack_ffn_bulk_t(const void* w1, const void* w2, void* packed, hipStream_t s)
+{
+    typedef FfnBulk<T, D> B;
+    const int64_t units = 4 * B::PASSES * B::FRAGS * 64;
+    hipLaunchKernelGGL((pack_ffn_bulk_kernel<T, D>), dim3((unsigned)((units + 255) / 256)), dim3(256), 0, s,
+                       (const T*)w1, (const T*)w2, (T*)packed);
+    return hipGetLastError();
+}
+template <typename T, int D>
+int launch_ffn_bulk_t(const dg4_ffn_args& a, hipStream_t s)
+{
+    typedef FfnBulk<T, D> B;
+    const int64_t rows = a.row_end - a.row_begin;
+    if (rows <= 0) return hipSuccess;
+    hipError_t e = hipFuncSetAttribute((const void*)ffn_bulk_kernel<T, D>, hipFuncAttributeMaxDynamicSharedMemorySize, B::SMEM);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((ffn_bulk_kernel<T, D>), dim3((unsigned)((rows + B::ROWS - 1) / B::ROWS)), dim3(256), B::SMEM, s, a);
+    return hipGetLastError();
 }
 
 template <typename T, int D>
@@ -1073,22 +1159,16 @@ int dg4_launch_pack_w2(int dtype, const void* w2, int hidden, void* packed, hipS
     return hipGetLastError();
 }
 
-int dg4_launch_pack_ffn_bulk(const void* w1, const void* w2, void* packed, hipStream_t s)
+int dg4_launch_pack_ffn_bulk(int dtype, int hidden, const void* w1, const void* w2, void* packed, hipStream_t s)
 {
-    const int64_t units = 4 * FB_PASSES * FB_FRAGS * 64;
-    hipLaunchKernelGGL(pack_ffn_bulk_kernel, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, s,
-                       (const uint16_t*)w1, (const uint16_t*)w2, (uint16_t*)packed);
-    return hipGetLastError();
+    if (dtype == DG4_F32) return hidden == 128 ? launch_pack_ffn_bulk_t<float, 128>(w1, w2, packed, s) : launch_pack_ffn_bulk_t<float, 256>(w1, w2, packed, s);
+    return hidden == 128 ? launch_pack_ffn_bulk_t<bf16_t, 128>(w1, w2, packed, s) : launch_pack_ffn_bulk_t<bf16_t, 256>(w1, w2, packed, s);
 }
 
-int dg4_launch_ffn_bulk(const dg4_ffn_args& a, hipStream_t s)
+int dg4_launch_ffn_bulk(int dtype, int hidden, const dg4_ffn_args& a, hipStream_t s)
 {
-    const int64_t rows = a.row_end - a.row_begin;
-    if (rows <= 0) return hipSuccess;
-    hipError_t e = hipFuncSetAttribute((const void*)ffn_bulk_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FB_SMEM);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(ffn_bulk_kernel, dim3((unsigned)((rows + FB_ROWS - 1) / FB_ROWS)), dim3(256), FB_SMEM, s, a);
-    return hipGetLastError();
+    if (dtype == DG4_F32) return hidden == 128 ? launch_ffn_bulk_t<float, 128>(a, s) : launch_ffn_bulk_t<float, 256>(a, s);
+    return hidden == 128 ? launch_ffn_bulk_t<bf16_t, 128>(a, s) : launch_ffn_bulk_t<bf16_t, 256>(a, s);
 }
 
 int dg4_launch_ffn(int dtype, int hidden, const dg4_ffn_args& a, hipStream_t s)
