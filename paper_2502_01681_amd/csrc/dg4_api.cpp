@@ -462,15 +462,17 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
     // One persistent dataflow kernel for the whole range of levels (with the feed-forward sub-block:
     // whole-graph sweeps only, partial ones run level by level)
     if (resident) {
-        // A sweep over all levels runs in the dependency-driven tile order, a partial one (resume)
-        // or one with DG4_LEVEL_ORDER level by level; rows of the internal buffers are positions in
-        // the order in use.
-        const bool whole = whole_range && (ffn || !(cfg->flags & DG4_LEVEL_ORDER));
-        if (ffn) {
-            rc = dg4_graph_ensure_pairs(g);
-            if (rc != DG4_OK) return rc;
-        }
-        const int32_t* order_in_use = ffn ? g->d_pair_order : whole ? g->d_flow_order : g->d_order;
+        // A sweep over all levels runs in the dependency-driven tile order (or level by level where that is
+        // as good), a partial one (resume) or one with DG4_LEVEL_ORDER level by level; rows of the internal
+        // buffers are positions in the order in use.
+        const bool by_level = dg4_sweeps_by_level(g, ffn);
+        const bool whole = whole_range && !by_level && (ffn || !(cfg->flags & DG4_LEVEL_ORDER));
+        const bool pairs = ffn && !by_level;
+        const dg4_graph::LevelTiles* lt = nullptr;
+        if (by_level) rc = ffn ? dg4_graph_ensure_level_pairs(g, &lt) : dg4_graph_ensure_level_tiles(g, dg4_sweep_tile_rows(g), &lt);
+        else if (ffn) rc = dg4_graph_ensure_pairs(g);
+        if (rc != DG4_OK) return rc;
+        const int32_t* order_in_use = pairs ? g->d_pair_order : whole ? g->d_flow_order : g->d_order;
         {   // Q | K | V of x for every gate of the swept levels, rows in processing order
             if (pack) HIPCHK(dg4_launch_pack_w32(W[0], 3 * d, at(pl.wqkv[0]), s));
             dg4_bulk_args b{};
@@ -486,10 +488,11 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
             HIPCHK(dg4_launch_pack_wt(W[0], 3 * d, d, 8, 4, at(pl.wkv_t), s));
         }
         dg4_sweep_args a{};
-        a.tiles = ffn ? g->d_pair_tiles : whole ? g->d_flow_tiles : g->d_tiles;
-        a.tile_begin = whole ? 0 : g->level_tile_ptr[level_begin];
-        a.n_tiles = ffn ? g->n_pair_tiles : whole ? g->n_flow_tiles : g->level_tile_ptr[level_end] - a.tile_begin;
-        a.ell = ffn ? g->d_pair_ell : whole ? g->d_flow_ell : g->d_ell_pos; a.ell_w = g->ell_w;
+        a.tiles = pairs ? g->d_pair_tiles : whole ? g->d_flow_tiles : lt ? lt->d_tiles : g->d_tiles;
+        const std::vector<int64_t>& tile_ptr = lt ? lt->level_ptr : g->level_tile_ptr;
+        a.tile_begin = whole ? 0 : tile_ptr[level_begin];
+        a.n_tiles = pairs ? g->n_pair_tiles : whole ? g->n_flow_tiles : tile_ptr[level_end] - a.tile_begin;
+        a.ell = pairs ? g->d_pair_ell : whole ? g->d_flow_ell : g->d_ell_pos; a.ell_w = g->ell_w;
         a.order = order_in_use;
         a.x = (const uint16_t*)X;
         a.qkv_self = (const uint16_t*)at(pl.qkv_self);
@@ -503,7 +506,7 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
             a.park = (uint16_t*)at(pl.park);
         }
         a.flags = (uint32_t*)at(pl.flags); a.ctrl = (uint32_t*)at(pl.ctrl);
-        a.ln_eps = cfg->ln_eps; a.epilogue = epi ? 1 : 0; a.eager_publish = whole ? 0 : 1;
+        a.ln_eps = cfg->ln_eps; a.epilogue = epi ? 1 : 0; a.eager_publish = whole || ffn ? 0 : 1;
         a.spin_limit = spin_limit;
         a.prof = (cfg->flags & DG4_PROFILE) ? (uint64_t*)((char*)at(pl.ctrl) + 64) : nullptr;
         HIPCHK(dg4_launch_sweep_init(a.flags, a.ctrl, g->n, P0, s));

@@ -754,36 +754,51 @@ int dg4_graph_ensure_pairs(dg4_graph* g)
 // Device tables: fixed-width packed rows, once by node id (for calls whose
 // tensors are indexed by id) and once by position in the (level, id) order
 // (for the sweep, whose internal buffers are level sorted).
-// Runs of at most `rows` positions inside a level. The caller holds g->mu.
-static int level_tiles(dg4_graph* g, int rows, const dg4_graph::LevelTiles** out)
+// Runs of at most `rows` positions inside a level, as many tiles per level as a multiple of `group` (the last may be
+// empty). The caller holds g->mu.
+static int level_tiles(dg4_graph* g, int rows, int group, dg4_graph::LevelTiles& lt)
 {
-    const int slot = rows == 2 ? 0 : rows == 4 ? 1 : rows == 8 ? 2 : rows == 16 ? 3 : -1;
-    if (slot < 0) return DG4_EINVAL;
-    dg4_graph::LevelTiles& lt = g->level_tiles[slot];
-    if (!lt.d_tiles) {
-        try {
-            std::vector<uint2> tiles;
-            std::vector<int64_t> ptr((size_t)g->max_level + 2, 0);
-            for (int32_t l = 0; l <= g->max_level; ++l) {
-                ptr[l] = (int64_t)tiles.size();
-                for (int64_t p0 = g->level_ptr[l]; p0 < g->level_ptr[l + 1]; p0 += rows)
-                    tiles.push_back(make_uint2((uint32_t)p0, (uint32_t)std::min<int64_t>(rows, g->level_ptr[l + 1] - p0)));
-            }
-            ptr[(size_t)g->max_level + 1] = (int64_t)tiles.size();
-            uint2* d = nullptr;
-            if (hipMalloc((void**)&d, std::max<size_t>(tiles.size(), 1) * sizeof(uint2)) != hipSuccess) return DG4_ENOMEM;
-            if (!tiles.empty() && hipMemcpy(d, tiles.data(), tiles.size() * sizeof(uint2), hipMemcpyHostToDevice) != hipSuccess) {
-                (void)hipFree(d);
-                return DG4_EHIP;
-            }
-            lt.level_ptr.swap(ptr);
-            lt.d_tiles = d;
-        } catch (const std::bad_alloc&) {
-            return DG4_ENOMEM;
+    if (lt.d_tiles) return DG4_OK;
+    try {
+        std::vector<uint2> tiles;
+        std::vector<int64_t> ptr((size_t)g->max_level + 2, 0);
+        for (int32_t l = 0; l <= g->max_level; ++l) {
+            ptr[l] = (int64_t)tiles.size();
+            for (int64_t p0 = g->level_ptr[l]; p0 < g->level_ptr[l + 1]; p0 += rows)
+                tiles.push_back(make_uint2((uint32_t)p0, (uint32_t)std::min<int64_t>(rows, g->level_ptr[l + 1] - p0)));
+            while (tiles.size() % (size_t)group) tiles.push_back(make_uint2((uint32_t)g->level_ptr[l + 1], 0));
         }
+        ptr[(size_t)g->max_level + 1] = (int64_t)tiles.size();
+        uint2* d = nullptr;
+        if (hipMalloc((void**)&d, std::max<size_t>(tiles.size(), 1) * sizeof(uint2)) != hipSuccess) return DG4_ENOMEM;
+        if (!tiles.empty() && hipMemcpy(d, tiles.data(), tiles.size() * sizeof(uint2), hipMemcpyHostToDevice) != hipSuccess) {
+            (void)hipFree(d);
+            return DG4_EHIP;
+        }
+        lt.level_ptr.swap(ptr);
+        lt.d_tiles = d;
+    } catch (const std::bad_alloc&) {
+        return DG4_ENOMEM;
     }
-    if (out) *out = &lt;
     return DG4_OK;
+}
+static dg4_graph::LevelTiles& tiles_of(dg4_graph* g, int rows) { return g->level_tiles[rows == 2 ? 0 : rows == 4 ? 1 : rows == 8 ? 2 : 3]; }
+
+int dg4_graph_ensure_level_tiles(dg4_graph* g, int rows, const dg4_graph::LevelTiles** out)
+{
+    if (rows != 2 && rows != 4 && rows != 8 && rows != 16) return DG4_EINVAL;
+    std::lock_guard<std::mutex> lock(g->mu);
+    if (!g->on_device) return DG4_EINVAL;
+    *out = &tiles_of(g, rows);
+    return level_tiles(g, rows, 1, tiles_of(g, rows));
+}
+
+int dg4_graph_ensure_level_pairs(dg4_graph* g, const dg4_graph::LevelTiles** out)
+{
+    std::lock_guard<std::mutex> lock(g->mu);
+    if (!g->on_device) return DG4_EINVAL;
+    *out = &g->level_pairs;
+    return level_tiles(g, DG4_TILE_ROWS, 2, g->level_pairs);
 }
 
 int dg4_graph_ensure_device(dg4_graph* g)
@@ -800,7 +815,7 @@ int dg4_graph_ensure_device(dg4_graph* g)
         for (int64_t v = 0; v < g->n; ++v) longest = std::max(longest, g->nbr_ptr[v + 1] - g->nbr_ptr[v]);
         w = std::max(w, (int)((longest + 3) / 4 * 4));
     }
-    const bool with_flow = g->hops <= 2;       // the persistent sweep's tables
+    const bool with_flow = g->hops <= 2 && !dg4_sweeps_by_level(g, false);       // the persistent sweep's tables
     // two tables of rows x w entries are staged in host memory and copied: refuse what cannot fit
     // (a graph of copies without marks at k = 8 can have tens of millions of rows 512 wide)
     if (((size_t)g->n + DG4_TILE_ROWS) * (size_t)w * sizeof(uint32_t) > ((size_t)16 << 30)) return DG4_ENOMEM;
@@ -963,7 +978,9 @@ int dg4_graph_ensure_device(dg4_graph* g)
     // tiles for the kernel that spreads heads over compute units, both numbers of heads (now, so that a sweep after
     // dg4_graph_upload allocates nothing; if it fails here, that sweep tries again); wide circuits never take it
     if (dg4_dependency_width(g) <= 4 * DG4_HEADS_ROWS * dg4_head_groups(4))
-        for (int heads : {4, 8}) (void)level_tiles(g, dg4_heads_tile_rows(g, heads), nullptr);
+        for (int heads : {4, 8}) (void)level_tiles(g, dg4_heads_tile_rows(g, heads), 1, tiles_of(g, dg4_heads_tile_rows(g, heads)));
+    if (dg4_sweeps_by_level(g, false)) (void)level_tiles(g, dg4_sweep_tile_rows(g), 1, tiles_of(g, dg4_sweep_tile_rows(g)));
+    if (dg4_sweeps_by_level(g, true)) (void)level_tiles(g, DG4_TILE_ROWS, 2, g->level_pairs);
     g->ell_w = w; g->device = dev; g->on_device = true;
     return DG4_OK;
 }
@@ -998,13 +1015,6 @@ int dg4_graph_ensure_wide_tiles(dg4_graph* g)
         return DG4_ENOMEM;
     }
     return DG4_OK;
-}
-
-int dg4_graph_ensure_level_tiles(dg4_graph* g, int rows, const dg4_graph::LevelTiles** out)
-{
-    std::lock_guard<std::mutex> lock(g->mu);
-    if (!g->on_device) return DG4_EINVAL;
-    return level_tiles(g, rows, out);
 }
 
 // Device tables of the (Eq. 1 level, id) order, see dg4_graph::eq1_level_ptr.
@@ -1152,6 +1162,7 @@ extern "C" void dg4_graph_free(dg4_graph* g)
     if (g->d_pair_tiles) (void)hipFree(g->d_pair_tiles);
     for (const dg4_graph::LevelTiles& lt : g->level_tiles)
         if (lt.d_tiles) (void)hipFree(lt.d_tiles);
+    if (g->level_pairs.d_tiles) (void)hipFree(g->level_pairs.d_tiles);
     if (g->d_order_eq1) (void)hipFree(g->d_order_eq1);
     if (g->d_ell_eq1) (void)hipFree(g->d_ell_eq1);
     delete g;

@@ -532,7 +532,7 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
     hipStream_t s = (hipStream_t)stream;
     try {
         std::unique_ptr<dg4_graph> g(new dg4_graph());
-        g->n = n; g->e = e; g->hops = hops;
+        g->n = n; g->e = e; g->hops = hops; g->device_hint = level_hint != nullptr;
         if (n == 0) {
             g->level_ptr.assign(2, 0); g->nbr_ptr.assign(1, 0);
             if (stride > 0) { g->cone_group_ptr.assign(1, 0); g->stride = stride; g->batch_cones = batch; }

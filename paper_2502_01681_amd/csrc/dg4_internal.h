@@ -40,6 +40,7 @@ struct dg4_graph {
     // Partitioned graphs (dg4_build_partitioned): Algorithm 1's lists; with marks the mini-batch of
     // each gate; without marks the nodes are copies: the gate each stands for, each gate's last copy.
     int32_t stride = 0, batch_cones = 0;
+    bool device_hint = false;                    // built on the GPU with a caller's levelling (Eq. 1 levels not known)
     bool marks = true;
     std::vector<int32_t> cone_root, cone_group_level, stage;
     std::vector<int64_t> cone_group_ptr;
@@ -74,6 +75,7 @@ struct dg4_graph {
     // runs of at most 2, 4, 8, 16 positions inside one level (the kernel that spreads heads over compute units), on first use
     struct LevelTiles { std::vector<int64_t> level_ptr; uint2* d_tiles = nullptr; };
     LevelTiles level_tiles[4];
+    LevelTiles level_pairs;          // of 16, in pairs (2k, 2k+1; the second may be empty) that never straddle a level
     // A second processing order for sweeps over ALL levels: tiles filled by list scheduling over
     // the real dependencies (a gate goes as early as its sources allow, sources long finished
     // first), not level by level. Host copy (node ids in processing order, first position of
@@ -109,6 +111,27 @@ inline int64_t dg4_dependency_width(const dg4_graph* g)
     const int64_t depth = g->eq1_level_ptr.empty() ? (int64_t)g->max_level + 1 : (int64_t)g->eq1_level_ptr.size() - 1;
     return g->n / (depth > 0 ? depth : 1);
 }
+// Whether whole sweeps of the register-resident kernel go level by level (tiles inside the levels, in the order of
+// the level-sorted tables) and not through the list schedule, whose host work (70 ns per gate, more than the rest of
+// dg4_graph_upload; twice that for pairs) is then not done. A sweep by list / by level, ms, at gates per level: 1.37 /
+// 1.39 at 492; 0.900 / 0.899 at 870; 0.576 / 0.579 at 1507; 1.315 / 1.334 at 1869; 0.547 / 0.532 at 4786; 0.957 / 0.926
+// at 5728; 1.23 / 1.26 at 9693; 0.787 / 0.814 at 25,256; 1.88 / 1.95 at 40,163. So by level from 640 (below it the
+// chain from level to level is all that counts) to 8192; with the feed-forward sub-block (1.71 / 1.69 at 25,256) above
+// that too. Levels that are not known to be the circuit's own (a deeper levelling of the caller's, rows cut by a
+// partition) keep the list schedule.
+inline bool dg4_sweeps_by_level(const dg4_graph* g, bool ffn)
+{
+    const int64_t width = dg4_dependency_width(g);
+    return g->hops <= 2 && g->stride == 0 && !g->device_hint && g->eq1_level_ptr.empty() && width > 640 && (ffn || width <= 8192);
+}
+// Gates per tile there: the sizes of the list schedule (best of 2, 4, 8, 16 measured: 2 at 492 gates per level, 4 at 870,
+// 8 at 1507 and 1980, 16 at 4786)
+inline int dg4_sweep_tile_rows(const dg4_graph* g)
+{
+    int rows = 2;
+    while (rows < DG4_TILE_ROWS && dg4_dependency_width(g) > (int64_t)rows * DG4_SCHED_TILES_PER_LEVEL) rows *= 2;
+    return rows;
+}
 // Groups of workgroups, one workgroup per head, that 256 compute units hold
 inline int dg4_head_groups(int heads) { return 256 / heads; }
 // Gates per tile of a level where the heads are spread over compute units: one round of tiles over the groups, up
@@ -137,6 +160,7 @@ int dg4_graph_ensure_frontier(dg4_graph* g);           // after dg4_graph_ensure
 int dg4_graph_ensure_struct(dg4_graph* g);
 int dg4_graph_ensure_pairs(dg4_graph* g);              // after dg4_graph_ensure_device
 int dg4_graph_ensure_level_tiles(dg4_graph* g, int rows, const dg4_graph::LevelTiles** out);   // rows 2, 4, 8 or 16; after dg4_graph_ensure_device
+int dg4_graph_ensure_level_pairs(dg4_graph* g, const dg4_graph::LevelTiles** out);           // after dg4_graph_ensure_device
 int dg4_graph_ensure_wide_tiles(dg4_graph* g);         // after dg4_graph_ensure_device; graphs with rows wider than 16 entries
 int dg4_graph_ensure_eq1(dg4_graph* g);                // after dg4_graph_ensure_device; needs eq1_level_ptr
 
