@@ -37,40 +37,52 @@ __global__ void fanin_kernel(int64_t n, int64_t e, const int32_t* es, const int3
     finv[2 * v + slot] = ei[i];
 }
 
-// duplicated fanin pair; primary inputs start at level 0 and are done
-__global__ void fanin_check_kernel(int64_t n, const int32_t* fin, const int32_t* deg, int32_t* level, uint8_t* done, int* status)
+// duplicated fanin pair; primary inputs start at level 0, every other gate without one (-1). finished: the gates
+// that have a level, added up a workgroup at a time
+__global__ __launch_bounds__(256) void fanin_check_kernel(int64_t n, const int32_t* fin, const int32_t* deg, int32_t* level,
+                                                          unsigned long long* finished, int* status)
 {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= n) return;
-    if (deg[v] == 2 && fin[2 * v] == fin[2 * v + 1]) report(status, DG4_EFANIN);
-    level[v] = 0;
-    done[v] = deg[v] == 0;
-}
-
-// One round of Eq. 1: a gate whose fanins were all done BEFORE this round gets max + 1. Two flag
-// arrays alternate so that a round reads only the previous round's state (level[] of a fanin is
-// final once its flag is set). progress[0] counts the gates finished so far.
-__global__ void level_round_kernel(int64_t n, const int32_t* fin, const int32_t* deg, const uint8_t* done_in,
-                                   uint8_t* done_out, int32_t* level, unsigned long long* progress)
-{
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= n) return;
-    if (done_in[v]) { done_out[v] = 1; return; }
-    const int d = deg[v];
-    int32_t best = -1;
-    bool ready = true;
-    for (int k = 0; k < d; ++k) {
-        const int32_t u = fin[2 * v + k];
-        if (done_in[u]) best = max(best, level[u]); else ready = false;
+    const bool input = v < n && deg[v] == 0;
+    if (v < n) {
+        if (deg[v] == 2 && fin[2 * v] == fin[2 * v + 1]) report(status, DG4_EFANIN);
+        level[v] = input ? 0 : -1;
     }
-    if (ready) { level[v] = best + 1; atomicAdd(progress, 1ull); }
-    done_out[v] = ready;
+    const int count = __syncthreads_count(input);
+    if (threadIdx.x == 0 && count) atomicAdd(finished, (unsigned long long)count);
 }
 
-__global__ void count_done_kernel(int64_t n, const uint8_t* done, unsigned long long* progress)
+// Eq. 1: a gate whose fanins all have their level gets max + 1, which is final, so a level may be used as soon as it
+// can be seen and in any order: a gate looks again and again, ROUNDS times at most, and one launch carries many
+// levels (agent-scope accesses: the fanin may have been finished a moment ago on another XCD). What is
+// not finished by then is left to the next launch; a launch finishes at least the gates whose fanins were finished
+// before it. Bound by the trip to memory per level. (One level per launch and one counter update per
+// gate took 12 us a level on 102 K gates.)
+constexpr int LEVEL_ROUNDS = 64;
+__global__ __launch_bounds__(256) void level_round_kernel(int64_t n, const int32_t* fin, const int32_t* deg, int32_t* level,
+                                                          unsigned long long* finished)
 {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v < n && done[v]) atomicAdd(progress, 1ull);
+    bool open = v < n && __hip_atomic_load(&level[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < 0, mine = false;
+    int32_t a = -1, b = -1;                       // levels of the two fanins once seen
+    int32_t ua = 0, ub = 0;
+    if (open) {
+        ua = fin[2 * v];
+        if (deg[v] == 2) ub = fin[2 * v + 1]; else b = 0;         // (level 0 or above: no other fanin to wait for)
+    }
+    for (int r = 0; r < LEVEL_ROUNDS && __ballot(open) != 0; ++r) {
+        if (open) {
+            if (a < 0) a = __hip_atomic_load(&level[ua], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (b < 0) b = __hip_atomic_load(&level[ub], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (a >= 0 && b >= 0) {
+                __hip_atomic_store(&level[v], max(a, b) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                open = false; mine = true;
+            }
+        }
+        __builtin_amdgcn_s_sleep(2);
+    }
+    const int count = __syncthreads_count(mine);
+    if (threadIdx.x == 0 && count) atomicAdd(finished, (unsigned long long)count);
 }
 
 // a caller's levelling: non-negative, 0 exactly on primary inputs' side of the rule, strictly
@@ -547,15 +559,13 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
         GPU_ALLOC(finv, uint8_t, 2 * (size_t)n, true);
         GPU_ALLOC(deg, int32_t, (size_t)n, true);
         GPU_ALLOC(level, int32_t, (size_t)n, false);
-        GPU_ALLOC(done_a, uint8_t, (size_t)n, false);
-        GPU_ALLOC(done_b, uint8_t, (size_t)n, false);
         GPU_ALLOC(status, int, 1, true);
         GPU_ALLOC(progress, unsigned long long, 1, true);
         GPU_ALLOC(max_level, int32_t, 1, true);
         const unsigned nb = blocks_for(n);
 
         if (e > 0) hipLaunchKernelGGL(fanin_kernel, dim3(blocks_for(e)), dim3(256), 0, s, n, e, es, ed, ei, fin, finv, deg, status);
-        hipLaunchKernelGGL(fanin_check_kernel, dim3(nb), dim3(256), 0, s, n, fin, deg, level, done_a, status);
+        hipLaunchKernelGGL(fanin_check_kernel, dim3(nb), dim3(256), 0, s, n, fin, deg, level, progress, status);
         int st = 0;
         GPU_CHECK(hipMemcpyAsync(&st, status, sizeof(int), hipMemcpyDeviceToHost, s));
         GPU_CHECK(hipStreamSynchronize(s));
@@ -567,20 +577,16 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
             GPU_CHECK(hipStreamSynchronize(s));
             if (st != DG4_OK) return st;
         } else {
-            // rounds of Eq. 1, a batch at a time; no progress in a batch with gates left = a cycle
-            hipLaunchKernelGGL(count_done_kernel, dim3(nb), dim3(256), 0, s, n, done_a, progress);
+            // launches of Eq. 1 rounds, a batch at a time; no progress in a batch with gates left = a cycle
             unsigned long long finished = 0, before = ~0ull;
-            uint8_t* cur = done_a; uint8_t* nxt = done_b;
             for (;;) {
                 GPU_CHECK(hipMemcpyAsync(&finished, progress, sizeof(finished), hipMemcpyDeviceToHost, s));
                 GPU_CHECK(hipStreamSynchronize(s));
                 if (finished == (unsigned long long)n) break;
                 if (finished == before) return DG4_ECYCLE;
                 before = finished;
-                for (int r = 0; r < 32; ++r) {
-                    hipLaunchKernelGGL(level_round_kernel, dim3(nb), dim3(256), 0, s, n, fin, deg, cur, nxt, level, progress);
-                    std::swap(cur, nxt);
-                }
+                for (int r = 0; r < 2; ++r)
+                    hipLaunchKernelGGL(level_round_kernel, dim3(nb), dim3(256), 0, s, n, fin, deg, level, progress);
             }
         }
 
