@@ -720,15 +720,6 @@ int dg4_graph_ensure_pairs(dg4_graph* g)
         std::vector<uint2> tiles(tile_ptr.size() - 1);
         for (size_t t = 0; t + 1 < tile_ptr.size(); ++t)
             tiles[t] = make_uint2((uint32_t)tile_ptr[t], (uint32_t)(tile_ptr[t + 1] - tile_ptr[t]));
-        std::vector<uint32_t> ell(rows * w, DG4_ELL_PAD);
-        std::vector<int32_t> fpos((size_t)g->n, -1);
-        for (int64_t q = 0; q < g->n; ++q) fpos[(size_t)order[(size_t)q]] = (int32_t)q;
-        for (int64_t v = 0; v < g->n; ++v) {
-            const int64_t lo = g->nbr_ptr[v], cnt = g->nbr_ptr[v + 1] - lo;
-            uint32_t* r = &ell[(size_t)fpos[v] * w];
-            for (int64_t j = 0; j < cnt; ++j)
-                r[j] = ((uint32_t)g->nbr_rel[lo + j] << 30) | (uint32_t)fpos[g->nbr_idx[lo + j]];
-        }
         uint32_t* d_ell = nullptr; int32_t* d_order = nullptr; uint2* d_tiles = nullptr;
         auto fail = [&](int code) {
             if (d_ell) (void)hipFree(d_ell);
@@ -739,8 +730,10 @@ int dg4_graph_ensure_pairs(dg4_graph* g)
         if (hipMalloc((void**)&d_ell, rows * w * sizeof(uint32_t)) != hipSuccess) return fail(DG4_ENOMEM);
         if (hipMalloc((void**)&d_order, rows * sizeof(int32_t)) != hipSuccess) return fail(DG4_ENOMEM);
         if (hipMalloc((void**)&d_tiles, std::max<size_t>(tiles.size(), 1) * sizeof(uint2)) != hipSuccess) return fail(DG4_ENOMEM);
-        if (hipMemcpy(d_ell, ell.data(), rows * w * sizeof(uint32_t), hipMemcpyHostToDevice) != hipSuccess) return fail(DG4_EHIP);
         if (hipMemcpy(d_order, padded.data(), rows * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess) return fail(DG4_EHIP);
+        const int32_t* orders[] = { d_order };
+        uint32_t* tables[] = { d_ell };
+        if (const int code = dg4_pack_rows(g, w, (int64_t)rows, 1, orders, tables); code != DG4_OK) return fail(code);
         if (!tiles.empty() && hipMemcpy(d_tiles, tiles.data(), tiles.size() * sizeof(uint2), hipMemcpyHostToDevice) != hipSuccess) return fail(DG4_EHIP);
         g->d_pair_ell = d_ell; g->d_pair_order = d_order; g->d_pair_tiles = d_tiles;
         g->n_pair_tiles = (int64_t)tiles.size();
@@ -816,7 +809,7 @@ int dg4_graph_ensure_device(dg4_graph* g)
         w = std::max(w, (int)((longest + 3) / 4 * 4));
     }
     const bool with_flow = g->hops <= 2 && !dg4_sweeps_by_level(g, false);       // the persistent sweep's tables
-    // two tables of rows x w entries are staged in host memory and copied: refuse what cannot fit
+    // two tables of rows x w entries: refuse what cannot fit
     // (a graph of copies without marks at k = 8 can have tens of millions of rows 512 wide)
     if (((size_t)g->n + DG4_TILE_ROWS) * (size_t)w * sizeof(uint32_t) > ((size_t)16 << 30)) return DG4_ENOMEM;
     // one tile of padding: the sweep kernel fetches descriptors of 16 positions at a time
@@ -828,58 +821,63 @@ int dg4_graph_ensure_device(dg4_graph* g)
         // that gates whose sources are old share tiles and only the last tiles of a level wait on
         // the levels just before. (The published `order` table keeps (level, id); results do not
         // depend on this.)
-        // (three independent derivations, on three threads: the level-sorted tables, the table by node id,
-        // the dependency-driven schedule with its table)
+        // (two independent derivations, on two threads: the level-sorted order and the list schedule; the tables
+        // themselves are packed on the device)
         std::vector<int32_t> sweep(rows, 0);
-        std::vector<uint32_t> by_id, by_pos, by_flow;
         std::vector<int32_t> flow;
         std::vector<uint2> flow_tiles;
-        int rc_job[3] = {DG4_OK, DG4_OK, DG4_OK};
+        int rc_job[2] = {DG4_OK, DG4_OK};
         auto guarded = [&](int slot, auto&& body) {
             try { body(); } catch (const std::bad_alloc&) { rc_job[slot] = DG4_ENOMEM; }
         };
         auto job_levels = [&]() { guarded(0, [&]() {
+            // (whole cones: the first reader of a gate is a direct one and its latest source a direct fanin, as
+            // levels rise along every edge; rows cut by a partition may lack a fanin and are looked at whole)
+            const bool direct = g->stride == 0;
+            auto counts = [&](int64_t j, int64_t v) { return direct ? g->nbr_rel[j] == 1 || g->nbr_rel[j] == 2 : g->nbr_idx[j] != v; };
             std::vector<int32_t> min_reader((size_t)g->n, INT32_MAX);
             for (int64_t v = 0; v < g->n; ++v)
-                for (int64_t j = g->nbr_ptr[v]; j < g->nbr_ptr[v + 1]; ++j) {
-                    const int32_t u = g->nbr_idx[j];
-                    if (u != v) min_reader[u] = std::min(min_reader[u], g->level[v]);
-                }
-            std::vector<int64_t> key((size_t)g->n, -1);
+                for (int64_t j = g->nbr_ptr[v]; j < g->nbr_ptr[v + 1]; ++j)
+                    if (counts(j, v)) min_reader[g->nbr_idx[j]] = std::min(min_reader[g->nbr_idx[j]], g->level[v]);
+            // Per level a stable counting sort by (read late, position of the latest source): on the circuit's own
+            // levels every gate has a fanin one level down, so these positions span one level. A wider span
+            // (a caller's levelling) is sorted by comparison, the same order. (100 K gates, 107 levels: 3.4 ms
+            // sorting by comparison.)
+            std::vector<int64_t> latest_of;
+            std::vector<std::pair<int64_t, int32_t>> keyed;
+            std::vector<int32_t> first;
             for (int32_t l = 0; l <= g->max_level; ++l) {
                 const int64_t lo = g->level_ptr[l], hi = g->level_ptr[l + 1];
+                int64_t least = INT64_MAX, most = -1;
+                latest_of.clear();
                 for (int64_t q = lo; q < hi; ++q) {
                     const int32_t v = g->order[q];
                     int64_t latest = -1;
                     for (int64_t j = g->nbr_ptr[v]; j < g->nbr_ptr[v + 1]; ++j)
-                        if (g->nbr_idx[j] != v) latest = std::max<int64_t>(latest, g->pos[g->nbr_idx[j]]);
-                    const int64_t far = (int64_t)min_reader[v] - l > 2 ? 1 : 0;
-                    key[v] = (far << 40) + latest + 1;
-                    sweep[q] = v;
+                        if (counts(j, v)) latest = std::max<int64_t>(latest, g->pos[g->nbr_idx[j]]);
+                    latest_of.push_back(latest);
+                    least = std::min(least, latest); most = std::max(most, latest);
                 }
-                std::stable_sort(sweep.begin() + lo, sweep.begin() + hi,
-                                 [&](int32_t a, int32_t b) { return key[a] < key[b]; });
-                for (int64_t q = lo; q < hi; ++q) g->pos[sweep[q]] = (int32_t)q;   // sources of higher levels see these
+                const int64_t span = hi > lo ? most - least + 1 : 0;
+                auto far = [&](int32_t v) { return (int64_t)min_reader[v] - l > 2; };
+                if (span <= 2 * (hi - lo) + 4096) {
+                    first.assign((size_t)(2 * span) + 1, 0);
+                    auto key = [&](int64_t q) { return (size_t)((far(g->order[q]) ? span : 0) + latest_of[(size_t)(q - lo)] - least); };
+                    for (int64_t q = lo; q < hi; ++q) ++first[key(q) + 1];
+                    for (size_t k = 0; k < (size_t)(2 * span); ++k) first[k + 1] += first[k];
+                    for (int64_t q = lo; q < hi; ++q) sweep[(size_t)(lo + first[key(q)]++)] = g->order[q];
+                } else {
+                    keyed.clear();
+                    for (int64_t q = lo; q < hi; ++q) {
+                        const int32_t v = g->order[q];
+                        keyed.emplace_back((int64_t)far(v) << 40 | (latest_of[(size_t)(q - lo)] + 1), v);
+                    }
+                    std::sort(keyed.begin(), keyed.end());                    // (ids ascend inside a level)
+                    for (int64_t q = lo; q < hi; ++q) sweep[(size_t)q] = keyed[(size_t)(q - lo)].second;
+                }
+                for (int64_t q = lo; q < hi; ++q) g->pos[sweep[(size_t)q]] = (int32_t)q;      // sources of higher levels see these
             }
             g->sweep_order.assign(sweep.begin(), sweep.begin() + g->n);
-            by_pos.assign(rows * w, DG4_ELL_PAD);
-            for (int64_t v = 0; v < g->n; ++v) {
-                const int64_t lo = g->nbr_ptr[v], cnt = g->nbr_ptr[v + 1] - lo;
-                uint32_t* rpos = &by_pos[(size_t)g->pos[v] * w];
-                for (int64_t j = 0; j < cnt; ++j)
-                    rpos[j] = ((uint32_t)g->nbr_rel[lo + j] << 30) | (uint32_t)g->pos[g->nbr_idx[lo + j]];
-            }
-        }); };
-        // entries stay in ascending-id order in every table, so the summation order of a gate's sources
-        // does not depend on the schedule
-        auto job_id = [&]() { guarded(1, [&]() {
-            by_id.assign(rows * w, DG4_ELL_PAD);
-            for (int64_t v = 0; v < g->n; ++v) {
-                const int64_t lo = g->nbr_ptr[v], cnt = g->nbr_ptr[v + 1] - lo;
-                uint32_t* rid = &by_id[(size_t)v * w];
-                for (int64_t j = 0; j < cnt; ++j)
-                    rid[j] = ((uint32_t)g->nbr_rel[lo + j] << 30) | (uint32_t)g->nbr_idx[lo + j];
-            }
         }); };
         std::vector<uint2> tiles;
         g->level_tile_ptr.assign((size_t)g->max_level + 2, 0);
@@ -898,37 +896,25 @@ int dg4_graph_ensure_device(dg4_graph* g)
         }
         g->level_tile32_ptr[(size_t)g->max_level + 1] = (int64_t)tiles32.size();
         // Dataflow order for whole-graph sweeps (dg4_flow_schedule)
-        auto job_flow = [&]() { guarded(2, [&]() {
+        auto job_flow = [&]() { guarded(1, [&]() {
             if (!with_flow) return;
             const int rc = dg4_flow_schedule(g);
-            if (rc != DG4_OK) { rc_job[2] = rc; return; }
+            if (rc != DG4_OK) { rc_job[1] = rc; return; }
             flow.assign(rows, 0);
             std::copy(g->flow_order.begin(), g->flow_order.end(), flow.begin());
             flow_tiles.resize(g->flow_tile_ptr.size() - 1);
             for (size_t t = 0; t + 1 < g->flow_tile_ptr.size(); ++t)
                 flow_tiles[t] = make_uint2((uint32_t)g->flow_tile_ptr[t], (uint32_t)(g->flow_tile_ptr[t + 1] - g->flow_tile_ptr[t]));
-            by_flow.assign(rows * w, DG4_ELL_PAD);
-            std::vector<int32_t> fpos((size_t)g->n, -1);
-            for (int64_t q = 0; q < g->n; ++q) fpos[(size_t)g->flow_order[(size_t)q]] = (int32_t)q;
-            for (int64_t v = 0; v < g->n; ++v) {
-                const int64_t lo = g->nbr_ptr[v], cnt = g->nbr_ptr[v + 1] - lo;
-                uint32_t* r = &by_flow[(size_t)fpos[v] * w];
-                for (int64_t j = 0; j < cnt; ++j)
-                    r[j] = ((uint32_t)g->nbr_rel[lo + j] << 30) | (uint32_t)fpos[g->nbr_idx[lo + j]];
-            }
             g->n_flow_tiles = (int64_t)flow_tiles.size();
         }); };
         {
-            std::vector<std::thread> helpers;
+            std::thread helper;
             try {
-                helpers.emplace_back(job_id);
-                helpers.emplace_back(job_flow);
-            } catch (const std::system_error&) {}      // no thread to be had: the jobs run here
+                if (with_flow) helper = std::thread(job_flow);
+            } catch (const std::system_error&) {}      // no thread to be had: the job runs here
             job_levels();
-            const size_t started = helpers.size();
-            for (std::thread& t : helpers) t.join();
-            if (started < 1) job_id();
-            if (started < 2) job_flow();
+            if (helper.joinable()) helper.join();
+            else job_flow();
         }
         for (int rc : rc_job)
             if (rc != DG4_OK) return rc;
@@ -957,8 +943,6 @@ int dg4_graph_ensure_device(dg4_graph* g)
         if (!tiles32.empty() &&
             hipMemcpy(g->d_tiles32, tiles32.data(), tiles32.size() * sizeof(uint2), hipMemcpyHostToDevice) != hipSuccess)
             return fail(DG4_EHIP);
-        if (hipMemcpy(g->d_ell_id, by_id.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) return fail(DG4_EHIP);
-        if (hipMemcpy(g->d_ell_pos, by_pos.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) return fail(DG4_EHIP);
         if (g->n > 0 &&
             hipMemcpy(g->d_order, sweep.data(), rows * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess)
             return fail(DG4_EHIP);
@@ -969,9 +953,13 @@ int dg4_graph_ensure_device(dg4_graph* g)
             if (!flow_tiles.empty() &&
                 hipMemcpy(g->d_flow_tiles, flow_tiles.data(), flow_tiles.size() * sizeof(uint2), hipMemcpyHostToDevice) != hipSuccess)
                 return fail(DG4_EHIP);
-            if (hipMemcpy(g->d_flow_ell, by_flow.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) return fail(DG4_EHIP);
             if (hipMemcpy(g->d_flow_order, flow.data(), rows * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess) return fail(DG4_EHIP);
         }
+        // entries stay in ascending-id order in every table, so the summation order of a gate's sources does not
+        // depend on the schedule
+        const int32_t* orders[] = { nullptr, g->d_order, g->d_flow_order };
+        uint32_t* tables[] = { g->d_ell_id, g->d_ell_pos, g->d_flow_ell };
+        if (const int rc = dg4_pack_rows(g, w, (int64_t)rows, with_flow ? 3 : 2, orders, tables); rc != DG4_OK) return fail(rc);
     } catch (const std::bad_alloc&) {
         return DG4_ENOMEM;
     }

@@ -534,6 +534,36 @@ inline unsigned blocks_for(int64_t items) { return (unsigned)((items + 255) / 25
 #define GPU_CHECK(expr) do { if ((expr) != hipSuccess) return DG4_EHIP; } while (0)
 #define GPU_ALLOC(var, T, count, zero) T* var = arena.get<T>((count), (zero), s); if (!var) return DG4_ENOMEM
 
+// position of every node in a processing order
+__global__ void position_kernel(int64_t n, const int32_t* order, int32_t* pos)
+{
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r < n) pos[order[r]] = (int32_t)r;
+}
+
+// One fixed-width table of packed neighbour rows: row r holds the row of node order[r] (null: r), entries by position
+// (null: by id) in ascending-id order, padded. Four entries per thread; bound by the table's own bytes and, by
+// position, the gather of the positions.
+__global__ __launch_bounds__(256) void pack_rows_kernel(int64_t n, int64_t rows, int w4, const int64_t* ptr, const int32_t* idx,
+                                                        const uint8_t* rel, const int32_t* order, const int32_t* pos, uint4* table)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= rows * w4) return;
+    const int64_t r = i / w4;
+    const int j0 = (int)(i % w4) * 4;
+    uint32_t e[4] = { DG4_ELL_PAD, DG4_ELL_PAD, DG4_ELL_PAD, DG4_ELL_PAD };
+    if (r < n) {
+        const int64_t v = order ? order[r] : r, lo = ptr[v], cnt = ptr[v + 1] - lo;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (j0 + q < cnt) {
+                const int32_t u = idx[lo + j0 + q];
+                e[q] = (uint32_t)rel[lo + j0 + q] << 30 | (uint32_t)(pos ? pos[u] : u);
+            }
+    }
+    table[i] = make_uint4(e[0], e[1], e[2], e[3]);
+}
+
 // stride == 0: plain cone rows; else the rows of the partitioned update with marks
 int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, const uint8_t* ei, int32_t hops,
                  const int32_t* level_hint, int32_t stride, int32_t batch, void* stream, dg4_graph** out)
@@ -766,6 +796,35 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
 }
 
 }  // namespace
+
+// The neighbour rows of g (host CSR) as `count` tables of rows x w entries on the current device, table i in the order
+// d_orders[i] (device, null: by node id). Synchronous, like the copies around it; temporary device memory of 12 bytes
+// per node and 5 per neighbour entry.
+int dg4_pack_rows(const dg4_graph* g, int w, int64_t rows, int count, const int32_t* const* d_orders, uint32_t* const* d_tables)
+{
+    if (w <= 0 || w % 4 || rows < g->n) return DG4_EINVAL;
+    hipStream_t s = nullptr;
+    const size_t n = (size_t)g->n, nnz = (size_t)g->nnz;
+    Arena arena;
+    if (!arena.reserve((n + 1) * 8 + nnz * 5 + n * 4 + 4096)) return DG4_ENOMEM;
+    GPU_ALLOC(ptr, int64_t, n + 1, false);
+    GPU_ALLOC(idx, int32_t, nnz, false);
+    GPU_ALLOC(rel, uint8_t, nnz, false);
+    GPU_ALLOC(pos, int32_t, n, false);
+    GPU_CHECK(hipMemcpy(ptr, g->nbr_ptr.data(), (n + 1) * 8, hipMemcpyHostToDevice));
+    if (nnz) {
+        GPU_CHECK(hipMemcpy(idx, g->nbr_idx.data(), nnz * 4, hipMemcpyHostToDevice));
+        GPU_CHECK(hipMemcpy(rel, g->nbr_rel.data(), nnz, hipMemcpyHostToDevice));
+    }
+    for (int t = 0; t < count; ++t) {
+        if (d_orders[t] && n) hipLaunchKernelGGL(position_kernel, dim3(blocks_for(g->n)), dim3(256), 0, s, g->n, d_orders[t], pos);
+        hipLaunchKernelGGL(pack_rows_kernel, dim3(blocks_for(rows * (w / 4))), dim3(256), 0, s, g->n, rows, w / 4, ptr, idx, rel,
+                           d_orders[t], d_orders[t] ? (const int32_t*)pos : (const int32_t*)nullptr, (uint4*)d_tables[t]);
+    }
+    GPU_CHECK(hipGetLastError());
+    GPU_CHECK(hipStreamSynchronize(s));
+    return DG4_OK;
+}
 
 extern "C" int dg4_build_levels_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed,
                                        const uint8_t* ei, int32_t hops, const int32_t* level_hint,

@@ -154,6 +154,8 @@ int dg4_qkv_proj_run(const dg4_layer_cfg* cfg, const void* S, int64_t row_begin,
                      const void* Wqkv, void* Q, void* K, void* V, void* packed, hipStream_t s);
 
 int dg4_graph_ensure_device(dg4_graph* g);
+// tables of packed neighbour rows on the device from the host CSR (dg4_graph_gpu.hip); d_orders[i] null: by node id
+int dg4_pack_rows(const dg4_graph* g, int w, int64_t rows, int count, const int32_t* const* d_orders, uint32_t* const* d_tables);
 int dg4_flow_schedule(dg4_graph* g);   // caller holds g->mu
 int dg4_pair_schedule(dg4_graph* g);   // caller holds g->mu
 int dg4_graph_ensure_frontier(dg4_graph* g);           // after dg4_graph_ensure_device
