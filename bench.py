@@ -178,12 +178,20 @@ def main():
         return {"ms_wall": wall * 1e3 / steps, "ms_dev": ms_dev, "ms_with_packing": ms_cold,
                 "ms_kernel": float(np.mean(sweep_ms)) if len(sweep_ms) == steps else None, "H": H, "ws": ws, "cfg": hot}
 
-    def path_of(c, g, flags):
+    def path_of(c, g, flags, depth=None):
+        """The kernel a sweep takes; depth: the circuit's own (Eq. 1) depth, where the graph's levels are deeper."""
         if flags.get("per_level") or flags.get("bounded_kv"):
             return "level-by-level launches"
+        ffn = bool(flags.get("ffn"))
+        if c.dtype == "bf16" and c.hidden == 256 and c.n_layers == 1 and g.hops <= 2 and not ffn:
+            return "sweep_kernel (persistent, weights resident in registers)"
+        streamed = (c.dtype, c.hidden) in (("f32", 128), ("bf16", 256)) and (not ffn or g.hops <= 3)
+        gates_per_level = g.n // (depth or g.n_levels)
+        if gates_per_level <= 256 // c.heads * 16 * (4 if not streamed else 2 if g.hops >= 6 else 1):
+            return "heads_kernel (persistent, heads of a tile spread over compute units)"
         if c.dtype == "bf16" and c.hidden == 256 and c.n_layers == 1 and g.hops <= 2:
             return "sweep_kernel (persistent, weights resident in registers)"
-        if flags.get("ffn") and g.hops > 3:
+        if not streamed:
             return "level-by-level launches"
         return "flow_kernel (persistent, weights streamed" + (", several lane groups per neighbour row)" if g.hops > 3 else ")")
 
@@ -245,7 +253,7 @@ def main():
     # that the bulk projection hands it are an implementation detail and are NOT counted.
     achieved = compulsory / (ms_kernel * 1e-3) / 1e9
     persistent = r["ms_kernel"] is not None
-    kernel_name = path_of(c, g, flags).split(" ")[0] if persistent else "dg4_layer_fwd"
+    kernel_name = path_of(c, g, flags, depth_eq1).split(" ")[0] if persistent else "dg4_layer_fwd"
     out = {
         "metric": "edges/sec per sparse-attn layer fwd (level sweep)",
         "value": nnz * layers / (ms_step * 1e-3),
@@ -259,7 +267,7 @@ def main():
                                f"(Eq. 1 depth {depth_eq1}), {c.hops}-hop cones, hidden {c.hidden}, {c.heads} heads, "
                                f"{layers} layer(s); weights packed once before the timed region",
                    "gates": n_gates, "neighbour_edges": nnz, "aig_edges": int(len(w.edge_src)),
-                   "levels": g.n_levels, "eq1_depth": depth_eq1, "path": path_of(c, g, flags)},
+                   "levels": g.n_levels, "eq1_depth": depth_eq1, "path": path_of(c, g, flags, depth_eq1)},
         "roofline": {"bound": "hbm",
                      "kernel": f"{kernel_name} (persistent level sweep, " + ("tiles by assigned level)" if args.level_order else "dependency-driven tile order)") if persistent
                                else "dg4_layer_fwd (all launches of one step)",
@@ -388,7 +396,7 @@ def main():
             for label, f in fl.items():
                 rr = time_layer(cc, cg, CX, FW if f.get("ffn") else CW, steps, warmup, **f)
                 comp, gath = algorithmic_bytes(cg, rr["cfg"], cg.array("level") if f.get("bounded_kv") else lev)
-                res[label] = {"path": path_of(cc, cg, f), "step_ms_device": rr["ms_dev"], "kernel_ms": rr["ms_kernel"],
+                res[label] = {"path": path_of(cc, cg, f, int(lev.max()) + 1), "step_ms_device": rr["ms_dev"], "kernel_ms": rr["ms_kernel"],
                               "step_ms_device_with_weight_packing": rr["ms_with_packing"],
                               "edges_per_s": cg.nnz * cc.n_layers / (rr["ms_dev"] * 1e-3),
                               "gates_per_s": cg.n * cc.n_layers / (rr["ms_dev"] * 1e-3),
@@ -450,7 +458,7 @@ def main():
                             "dg4_build_partitioned_s": t_part, "dg4_build_partitioned_device_s": t_part_dev,
                             "gathered_GBps": pgath / (ms_part * 1e-3) / 1e9,
                             "compulsory_GBps": pcomp / (ms_part * 1e-3) / 1e9,
-                            "traffic": measured_traffic("medium_partition_k8_rocprofv3.txt", "flow_kernel")}
+                            "traffic": measured_traffic("medium_partition_k8_rocprofv3.txt", "heads_kernel")}
         del pr
         # ... and under the paper's transformer depth as well (Section 4.1: twelve layers): its own configuration
         pc12 = synth.Config(**{**pc.__dict__, "n_layers": 12})

@@ -110,3 +110,35 @@ def test_heads_kernel_bounded_wait_two_streams_and_packed_weights():
     for o, k in both:
         dg4.dg4_layer_status(cfg, g, k)
         assert torch.equal(o, H)
+
+
+@pytest.mark.parametrize("hidden,dtype,hops,ffn", [(128, "f32", 2, False), (256, "bf16", 3, False), (128, "bf16", 5, True)])
+def test_heads_kernel_under_graph_capture(hidden, dtype, hops, ffn):
+    # captured right after dg4_graph_upload (no sweep before it: nothing may be allocated), replayed with eager work
+    # and new inputs in between
+    w = make(900, 90, hidden, dtype, hops, 2)
+    c = w.cfg
+    fw = synth.ffn_weights(c) if ffn else None
+    g = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops)
+    g.upload()
+    cfg = cfg_of(c, ffn=ffn)
+    X, W = to_dev(w.x, dtype), device_weights(w, dtype)
+    if ffn:
+        W = [lw + (to_dev(fw[0][l], dtype), to_dev(fw[1][l], dtype)) for l, lw in enumerate(W)]
+    out = torch.full_like(X, float("nan"))
+    ws = torch.empty(dg4.dg4_layer_workspace_bytes(cfg, g), dtype=torch.uint8, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    print(f"heads kernel captured: {dtype} {hidden} hops={hops} ffn={ffn}", flush=True)
+    with torch.cuda.graph(graph):
+        dg4.dg4_layer_fwd(cfg, g, X, W, out, workspace=ws)
+    for replay in range(3):
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        dg4.dg4_layer_status(cfg, g, ws)
+        eager = torch.full_like(X, float("nan"))
+        dg4.dg4_layer_fwd(cfg, g, X, W, eager)
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager), replay
+        X.mul_(-1)
