@@ -364,7 +364,7 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
         const bool wide = g->ell_w > 16;
         dg4_heads_args a{};
         const int rows = dg4_heads_tile_rows(g, cfg->heads);
-        if (whole_range && !wide && !g->eq1_level_ptr.empty() && !(cfg->flags & DG4_LEVEL_ORDER)) {
+        if (whole_range && !wide && dg4_levels_deeper(g) && !(cfg->flags & DG4_LEVEL_ORDER)) {
             // a caller's levelling deeper than the circuit: the dependency-driven order, its tiles (8 or 16 gates) one
             // by one or, where a level holds more than the groups, two of 8 at a time (they never depend on each other)
             rc = dg4_graph_ensure_pairs(g);
@@ -557,8 +557,7 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
             // Tiles of 32 gates (two of the table's tiles of 16, which never depend on each other) share a
             // pass over the weights; on a deep, narrow circuit, where a level is a handful of tiles and
             // most compute units idle, tiles of 16 halve the matrix-core time on the dependency chain.
-            const int64_t depth = g->eq1_level_ptr.empty() ? (int64_t)g->max_level + 1 : (int64_t)g->eq1_level_ptr.size() - 1;
-            const bool narrow = g->n / std::max<int64_t>(depth, 1) < 4096;
+            const bool narrow = dg4_dependency_width(g) < 4096;
             a.tiles = g->d_pair_tiles; a.pairs = narrow ? 0 : 1; a.tile_begin = 0;
             a.n_tiles = narrow ? g->n_pair_tiles : g->n_pair_tiles / 2;
             a.tile_cap = narrow ? 16 : 32;

@@ -574,7 +574,7 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
     hipStream_t s = (hipStream_t)stream;
     try {
         std::unique_ptr<dg4_graph> g(new dg4_graph());
-        g->n = n; g->e = e; g->hops = hops; g->device_hint = level_hint != nullptr;
+        g->n = n; g->e = e; g->hops = hops;
         if (n == 0) {
             g->level_ptr.assign(2, 0); g->nbr_ptr.assign(1, 0);
             if (stride > 0) { g->cone_group_ptr.assign(1, 0); g->stride = stride; g->batch_cones = batch; }
@@ -601,31 +601,42 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
         GPU_CHECK(hipStreamSynchronize(s));
         if (st != DG4_OK) return st;
 
+        int32_t* hinted = nullptr;
         if (level_hint) {
-            hipLaunchKernelGGL(hint_check_kernel, dim3(nb), dim3(256), 0, s, n, fin, deg, level_hint, level, status);
+            hinted = arena.get<int32_t>((size_t)n, false, s);
+            if (!hinted) return DG4_ENOMEM;
+            hipLaunchKernelGGL(hint_check_kernel, dim3(nb), dim3(256), 0, s, n, fin, deg, level_hint, hinted, status);
             GPU_CHECK(hipMemcpyAsync(&st, status, sizeof(int), hipMemcpyDeviceToHost, s));
             GPU_CHECK(hipStreamSynchronize(s));
             if (st != DG4_OK) return st;
-        } else {
-            // launches of Eq. 1 rounds, a batch at a time; no progress in a batch with gates left = a cycle
-            unsigned long long finished = 0, before = ~0ull;
-            for (;;) {
-                GPU_CHECK(hipMemcpyAsync(&finished, progress, sizeof(finished), hipMemcpyDeviceToHost, s));
-                GPU_CHECK(hipStreamSynchronize(s));
-                if (finished == (unsigned long long)n) break;
-                if (finished == before) return DG4_ECYCLE;
-                before = finished;
-                for (int r = 0; r < 2; ++r)
-                    hipLaunchKernelGGL(level_round_kernel, dim3(nb), dim3(256), 0, s, n, fin, deg, level, progress);
-            }
+        }
+        // launches of Eq. 1 rounds, a batch at a time; no progress in a batch with gates left = a cycle (with a
+        // caller's levelling only their depth is used: which kernel sweeps the graph goes by it)
+        unsigned long long finished = 0, before = ~0ull;
+        for (;;) {
+            GPU_CHECK(hipMemcpyAsync(&finished, progress, sizeof(finished), hipMemcpyDeviceToHost, s));
+            GPU_CHECK(hipStreamSynchronize(s));
+            if (finished == (unsigned long long)n) break;
+            if (finished == before) return DG4_ECYCLE;
+            before = finished;
+            for (int r = 0; r < 2; ++r)
+                hipLaunchKernelGGL(level_round_kernel, dim3(nb), dim3(256), 0, s, n, fin, deg, level, progress);
         }
 
         // (level, id) order: stable sort of the ids by level
         GPU_ALLOC(ids, int32_t, (size_t)n, false);
         GPU_ALLOC(sorted_level, int32_t, (size_t)n, false);
         GPU_ALLOC(order, int32_t, (size_t)n, false);
-        hipLaunchKernelGGL(iota_max_kernel, dim3(nb), dim3(256), 0, s, n, level, ids, max_level);
         int32_t h_max = 0;
+        if (hinted) {
+            GPU_ALLOC(own_max, int32_t, 1, true);
+            hipLaunchKernelGGL(iota_max_kernel, dim3(nb), dim3(256), 0, s, n, level, ids, own_max);
+            GPU_CHECK(hipMemcpyAsync(&h_max, own_max, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+            GPU_CHECK(hipStreamSynchronize(s));
+            g->own_depth = h_max + 1;
+            level = hinted;
+        }
+        hipLaunchKernelGGL(iota_max_kernel, dim3(nb), dim3(256), 0, s, n, level, ids, max_level);
         GPU_CHECK(hipMemcpyAsync(&h_max, max_level, sizeof(int32_t), hipMemcpyDeviceToHost, s));
         GPU_CHECK(hipStreamSynchronize(s));
         g->max_level = h_max;

@@ -40,7 +40,7 @@ struct dg4_graph {
     // Partitioned graphs (dg4_build_partitioned): Algorithm 1's lists; with marks the mini-batch of
     // each gate; without marks the nodes are copies: the gate each stands for, each gate's last copy.
     int32_t stride = 0, batch_cones = 0;
-    bool device_hint = false;                    // built on the GPU with a caller's levelling (Eq. 1 levels not known)
+    int64_t own_depth = 0;                       // built on the GPU with a caller's levelling: the number of Eq. 1 levels
     bool marks = true;
     std::vector<int32_t> cone_root, cone_group_level, stage;
     std::vector<int64_t> cone_group_ptr;
@@ -105,10 +105,16 @@ struct dg4_graph {
     int pair_tile_rows = 0;          // gates of its largest tile
 };
 
-// Gates per level of the dependencies a whole sweep follows
+// Levels of the dependencies a whole sweep follows (Eq. 1), whether the graph's own levelling is deeper, gates per level
+inline int64_t dg4_dependency_depth(const dg4_graph* g)
+{
+    if (!g->eq1_level_ptr.empty()) return (int64_t)g->eq1_level_ptr.size() - 1;
+    return g->own_depth > 0 ? g->own_depth : (int64_t)g->max_level + 1;
+}
+inline bool dg4_levels_deeper(const dg4_graph* g) { return dg4_dependency_depth(g) < (int64_t)g->max_level + 1; }
 inline int64_t dg4_dependency_width(const dg4_graph* g)
 {
-    const int64_t depth = g->eq1_level_ptr.empty() ? (int64_t)g->max_level + 1 : (int64_t)g->eq1_level_ptr.size() - 1;
+    const int64_t depth = dg4_dependency_depth(g);
     return g->n / (depth > 0 ? depth : 1);
 }
 // Whether whole sweeps of the register-resident kernel go level by level (tiles inside the levels, in the order of
@@ -122,7 +128,7 @@ inline int64_t dg4_dependency_width(const dg4_graph* g)
 inline bool dg4_sweeps_by_level(const dg4_graph* g, bool ffn)
 {
     const int64_t width = dg4_dependency_width(g);
-    return g->hops <= 2 && g->stride == 0 && !g->device_hint && g->eq1_level_ptr.empty() && width > 640 && (ffn || width <= 8192);
+    return g->hops <= 2 && g->stride == 0 && !dg4_levels_deeper(g) && width > 640 && (ffn || width <= 8192);
 }
 // Gates per tile there: the sizes of the list schedule (best of 2, 4, 8, 16 measured: 2 at 492 gates per level, 4 at 870,
 // 8 at 1507 and 1980, 16 at 4786)

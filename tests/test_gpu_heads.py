@@ -142,3 +142,44 @@ def test_heads_kernel_under_graph_capture(hidden, dtype, hops, ffn):
         torch.cuda.synchronize()
         assert torch.equal(out, eager), replay
         X.mul_(-1)
+
+
+@pytest.mark.parametrize("hidden,dtype,n_and,window,hops,ffn", [
+    (128, "f32", 900, 90, 2, False),        # a handful of gates per level: the list schedule's tiles one by one
+    (256, "bf16", 4_000, 3_000, 3, True),   # more than a round of its tiles of 8: two at a time
+    (128, "bf16", 700, 60, 5, False),       # wide rows: tiles cut from the caller's levels
+])
+def test_heads_kernel_on_a_deeper_levelling(hidden, dtype, n_and, window, hops, ffn):
+    # a caller's levelling deeper than Eq. 1 changes the schedule, not a bit of the result; host- and device-built
+    w = make(n_and, window, hidden, dtype, hops, 2)
+    c = w.cfg
+    fw = synth.ffn_weights(c) if ffn else None
+    cfg = cfg_of(c, ffn=ffn)
+    g = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops)
+    level = g.array("level")
+    hint = np.where(level > 0, 2 * level + np.arange(c.n_nodes) % 2, 0).astype(np.int32)
+    print(f"deeper levelling {dtype} {hidden} hops={hops}: {g.n_levels} levels of {c.n_nodes // g.n_levels}", flush=True)
+    H = run(w, cfg, g, fw)
+    deeper = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops, hint)
+    assert torch.equal(H, run(w, cfg, deeper, fw))
+    edges = [torch.from_numpy(a).cuda() for a in (w.edge_src, w.edge_dst, w.edge_inv)]
+    on_gpu = dg4.dg4_build_levels_device(c.n_nodes, *edges, hops, torch.from_numpy(hint).cuda())
+    assert torch.equal(H, run(w, cfg, on_gpu, fw))
+    assert torch.equal(H, run(w, cfg_of(c, ffn=ffn, level_order=True), deeper, fw))
+    mid = deeper.n_levels // 2
+    assert torch.equal(H, run(w, cfg, deeper, fw, mid, None, H0=run(w, cfg, deeper, fw, 0, mid)))
+
+
+def test_path_goes_by_the_circuits_own_depth():
+    # Eq. 1 depth 4 under a levelling of hundreds of levels: the path (and so every bit) is that of the wide circuit,
+    # whoever built the graph
+    w = synth.make(synth.Config("flat", 78, 500, 9_000, 4_000, 0.5, 3, 128, 4, 2, 2, "f32"))
+    c = w.cfg
+    cfg = cfg_of(c)
+    g = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, 2)
+    level = g.array("level")
+    hint = np.where(level > 0, 200 * level + np.arange(c.n_nodes) % 150, 0).astype(np.int32)
+    H = run(w, cfg, g)
+    edges = [torch.from_numpy(a).cuda() for a in (w.edge_src, w.edge_dst, w.edge_inv)]
+    assert torch.equal(H, run(w, cfg, dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, 2, hint)))
+    assert torch.equal(H, run(w, cfg, dg4.dg4_build_levels_device(c.n_nodes, *edges, 2, torch.from_numpy(hint).cuda())))
