@@ -45,6 +45,7 @@
 #include "dg4_device.h"
 #include "dg4_internal.h"
 #include "dg4_rowops.h"
+#include "dg4_wait.h"
 
 namespace {
 
@@ -381,14 +382,12 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
     };
     // (one thread) waits while `blocked()` holds; a wait in which the sweep's tickets still move is none to give up
     auto wait_while = [&](auto&& blocked) __attribute__((always_inline)) {
-        uint32_t spins = 0, seen = 0;
+        dg4_patience patience;
         while (blocked()) {
             __builtin_amdgcn_s_sleep(2);
-            if ((++spins & 63u) == 0 || spins > p.spin_limit) {
+            if (patience.look(p.spin_limit)) {
                 const uint32_t now = __hip_atomic_load(sweep_ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (spins > p.spin_limit && now != seen) spins = 0;
-                seen = now;
-                if (spins > p.spin_limit) __hip_atomic_store(&p.ctrl[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (patience.over(now, p.spin_limit)) __hip_atomic_store(&p.ctrl[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (__hip_atomic_load(&p.ctrl[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) { ctl[8] = 1; return; }
             }
         }
