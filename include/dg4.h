@@ -328,9 +328,11 @@ int dg4_sparse_attn_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, int64_t row_begi
  * Persistent sweeps (everything but DG4_PER_LEVEL, DG4_BOUNDED_KV and, on circuits with many gates per level,
  * DG4_FFN on rows wider than 16 entries and the shapes fp32 / 256 and bf16 / 128, which run level by level) hand
  * tiles of gates to resident workgroups, which wait for the
- * tiles their gates read from. Should such a wait exceed cfg->spin_limit polls (it cannot, unless
- * the device is taken away from the kernel), the sweep stops, Hout is left incomplete, and the
- * call has long returned DG4_OK: dg4_layer_status tells.
+ * tiles their gates read from. Any resident workgroup carries the sweep on; on circuits with few gates per
+ * level a tile is worked on by one workgroup per head, and any `heads` resident workgroups do. Should such a wait
+ * exceed cfg->spin_limit polls (it cannot, unless other work keeps all compute units, or there all but heads - 1 of
+ * them, from the kernel for that long), the sweep stops, Hout is left incomplete, and the call has long
+ * returned DG4_OK: dg4_layer_status tells.
  */
 int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void* X, const void* const* W,
                   int32_t level_begin, int32_t level_end, void* Hout,

@@ -24,12 +24,14 @@
 // Weights per layer and workgroup: Wo whole and 96 columns of Wq | Wk | Wv, every wave's fragments requested
 // one phase ahead into registers, so that a product waits for no memory.
 //
-// Order and progress: C consecutive workgroups, one per slice, form a GROUP and run through the same tiles
-// together; a group's first workgroup draws its tickets (one counter over the list of tiles) and hands them
-// to the others through a mailbox word. A group draws nothing before all its members have checked in, so a
-// ticket is only ever held by workgroups that run, and a tile waits for lower tickets only: the lowest
-// unfinished tile always advances as long as one group is resident (workgroups become resident in the order
-// of their numbers). Groups that never fill leave when the tickets have run out. A bounded spin count turns
+// Order and progress: C workgroups, one per slice, form a GROUP and run through the same tiles together; its
+// slice 0 draws the tickets (one counter over the list of tiles) and hands them to the others through a mailbox word.
+// Groups consist of workgroups that run (dg4_sit), so a ticket is only ever held by workgroups that run, and a tile
+// waits for lower tickets only: the lowest unfinished tile always advances as long as one group has formed. First C
+// workgroups with consecutive numbers look for each other (an XCD then sees one slice); should one of them not turn
+// up, because other work holds its compute units, the rest close the group and sit down in the order they come in,
+// each taking the slice of its place, so any C workgroups that run make a group, whatever else the device is
+// doing. Groups that never fill leave when the tickets have run out. A bounded spin count turns
 // any violation into an abort word. The exchange words of a group alternate between two places: a slice
 // writes the words of round k + 2 only after it has collected round k + 1 from all the others, each of which
 // had read round k before. (Tickets per slice, without groups, measured 11 us more per tile: the slices of a
@@ -52,8 +54,10 @@ namespace {
 constexpr int HT = 512;                       // threads (eight waves)
 constexpr int HR = DG4_HEADS_ROWS;            // most gates of a tile (one block of 16 of the matrix cores)
 // words (32 bits) of the sync area: ticket counters of the finished gates' tiles per slice, the ticket counter of
-// the sweep, check-in counters and (64-bit) mailboxes of the groups, every one 64 bytes from the next
-constexpr int SYNC_TICKET = 8 * 16, SYNC_ARRIVE = 9 * 16, SYNC_MAIL = SYNC_ARRIVE + DG4_HEADS_GROUPS * 16;
+// the sweep, the number of groups formed and of workgroups that look for another group, the words of the groups by
+// workgroup number and by order of arrival, and the (64-bit) mailboxes, every one 64 bytes from the next
+constexpr int SYNC_TICKET = 8 * 16, SYNC_FORMED = 9 * 16, SYNC_LOOSE = 10 * 16, SYNC_GROUP = 11 * 16,
+              SYNC_REGROUP = SYNC_GROUP + DG4_HEADS_GROUPS * 16, SYNC_MAIL = SYNC_REGROUP + DG4_HEADS_GROUPS * 16;
 static_assert((SYNC_MAIL + DG4_HEADS_GROUPS * 16) * 4 <= DG4_HEADS_SYNC_BYTES, "sync area");
 
 template <typename T> struct HeadMma;
@@ -227,7 +231,7 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
     T* qkv = (T*)(heads_smem + LDS::off_qkv);     // this head's Q | K | V of the running state
     float (*stat)[16][HR] = (float (*)[16][HR])(heads_smem + LDS::off_stat);     // [2][unit][row]
     float* att = (float*)(heads_smem + LDS::off_att);            // [part][32] weighted sums, then [part][2] maximum, denominator
-    int* ctl = (int*)(heads_smem + LDS::off_ctl); // this tile's and the next one's {first position, rows}, [8] abort word, [10] timer
+    int* ctl = (int*)(heads_smem + LDS::off_ctl); // this tile's and the next one's {first position, rows}, [8] abort word, [12], [13] place in a group
     float* biases = (float*)(ctl + 16);           // [layers][4] of this head
     uint32_t* ent = (uint32_t*)(heads_smem + LDS::off_ent);
     const int ell_w = W ? W : p.ell_w;
@@ -246,7 +250,7 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
     };
     phase(threadIdx.x);
     auto next_phase = [&]() __attribute__((always_inline)) { phase(tid); };
-    const int slice = (int)(blockIdx.x % C), group = (int)(blockIdx.x / C);
+    int slice = (int)(blockIdx.x % C);            // (until the workgroup has its seat)
     const int L = p.n_layers;
     const int64_t N = p.n_rows;
     uint32_t* flags = p.flags + (int64_t)slice * N;
@@ -367,7 +371,7 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
     };
 
     uint32_t* sweep_ticket = p.sync + SYNC_TICKET;
-    uint64_t* mail = (uint64_t*)(p.sync + SYNC_MAIL + group * 16);       // [2], by the parity of the tile's number in the group
+    uint64_t* mail = nullptr;                     // the group's [2], by the parity of the tile's number in the group
     auto tile_at = [&](int64_t t) __attribute__((always_inline)) -> uint2 {
         if (!p.pairs) return p.tiles[p.tile_begin + t];
         const uint2 ta = p.tiles[p.tile_begin + 2 * t], tb = p.tiles[p.tile_begin + 2 * t + 1];
@@ -430,8 +434,9 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
         if (!ctl[8] && tid < rows) __hip_atomic_store(&flags[p0 + tid], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     if (tid == 0) ctl[8] = 0;
-    if (tid < 4 * L) biases[tid] = p.rel_bias[(tid / 4 * C + slice) * 4 + tid % 4];
-    if (p.n_pre > 0) {
+    auto resume_slice = [&](int which) __attribute__((always_inline)) {
+        slice = which;
+        flags = p.flags + (int64_t)slice * N;
         for (;;) {
             if (tid == 0) ctl[0] = (int)__hip_atomic_fetch_add(&p.sync[slice * 16], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __syncthreads();
@@ -450,23 +455,67 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
             publish(p0, rows);
         }
         __syncthreads();
-    }
-    // ---- the group's first tile, once all its members run
-    if (tid == 0) {
-        uint32_t* arrived = p.sync + SYNC_ARRIVE + group * 16;
-        __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (slice == 0) {
-            wait_while([&]() {
-                return __hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)C &&
-                       __hip_atomic_load(sweep_ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)p.n_tiles;
-            });
-            if (__hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)C)
-                put_word(mail, (uint32_t)p.n_tiles, 1u);          // never filled, nothing left
-            else
-                post_ticket(0);
+    };
+    // ---- a seat in a group (first the group of the neighbouring workgroups, then any), and the group's first tile.
+    // A workgroup that changes its slice leaves no finished gate behind: whoever looks for another group has
+    // seen the tickets of every slice run out, and a group by number has one workgroup of every slice.
+    int place = -1;                               // group * C + slice; -1: the group was closed; -2: the sweep was given up
+    for (int stage = 0; stage < 2; ++stage) {
+        if (p.n_pre > 0) {
+            const int own = (int)(blockIdx.x % C);
+#pragma unroll 1
+            for (int i = stage; i < (stage ? C : 1); ++i) resume_slice((own + i) % C);
         }
-        receive(0);
+        if (tid == 0) {
+            struct {
+                const dg4_heads_args& p; uint32_t* ticket; int* ctl; dg4_patience patience;
+                __device__ uint32_t add(uint32_t* q) { return __hip_atomic_fetch_add(q, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+                __device__ uint32_t load(const uint32_t* q) { return __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+                __device__ void store(uint32_t* q, uint32_t v) { __hip_atomic_store(q, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+                __device__ bool cas(uint32_t* q, uint32_t expected, uint32_t v)
+                {
+                    return __hip_atomic_compare_exchange_strong(q, &expected, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                __device__ void pause() { __builtin_amdgcn_s_sleep(2); }
+                __device__ bool leave()           // nothing left, or the sweep was given up
+                {
+                    const uint32_t drawn = load(ticket);
+                    if (drawn >= (uint32_t)p.n_tiles) return true;
+                    if (patience.look(p.spin_limit)) {
+                        // (a ticket drawn and another workgroup come in are both movements)
+                        if (patience.over(drawn + load(p.sync + SYNC_LOOSE), p.spin_limit)) store(&p.ctrl[1], 1u);
+                        if (load(&p.ctrl[1])) { ctl[8] = 1; return true; }
+                    }
+                    return false;
+                }
+            } mem{p, sweep_ticket, ctl, {}};
+            int seat = (int)(blockIdx.x % C);
+            uint32_t* word = p.sync + SYNC_GROUP + (int)(blockIdx.x / C) * 16;
+            if (stage) {
+                const int arrival = (int)mem.add(p.sync + SYNC_LOOSE);
+                seat = arrival % C;
+                word = p.sync + SYNC_REGROUP + arrival / C * 16;
+            }
+            // (1024 polls, about a millisecond, at the default limit: workgroups of a launch on an idle device
+            // start within some microseconds of each other)
+            const dg4_seat at = dg4_sit(mem, word, (uint32_t)C, p.sync + SYNC_FORMED, stage ? 0xFFFFFFFFu : p.spin_limit >> 12);
+            ctl[12 + stage] = at.group >= 0 ? at.group * C + seat : ctl[8] ? -2 : -1;
+            if (at.group >= 0) {
+                mail = (uint64_t*)(p.sync + SYNC_MAIL + at.group * 16);
+                if (at.last) post_ticket(0);
+                receive(0);
+            }
+        }
+        __syncthreads();
+        place = __builtin_amdgcn_readfirstlane(ctl[12 + stage]);
+        if (place != -1) break;
     }
+    if (place < 0) return;
+    slice = place % C;
+    const int group = place / C;
+    flags = p.flags + (int64_t)slice * N;
+    mail = (uint64_t*)(p.sync + SYNC_MAIL + group * 16);
+    if (tid < 4 * L) biases[tid] = p.rel_bias[(tid / 4 * C + slice) * 4 + tid % 4];
     lap(-1);
     fill_qkv(0);
     uint64_t* xch = p.exchange + (int64_t)group * XT;

@@ -183,3 +183,44 @@ def test_path_goes_by_the_circuits_own_depth():
     edges = [torch.from_numpy(a).cuda() for a in (w.edge_src, w.edge_dst, w.edge_inv)]
     assert torch.equal(H, run(w, cfg, dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, 2, hint)))
     assert torch.equal(H, run(w, cfg, dg4.dg4_build_levels_device(c.n_nodes, *edges, 2, torch.from_numpy(hint).cuda())))
+
+
+@pytest.mark.parametrize("hidden,dtype,hops,ffn", [(256, "bf16", 2, False), (128, "f32", 3, False), (256, "f32", 2, True), (128, "bf16", 5, False)])
+def test_heads_kernel_in_groups_by_order_of_arrival(hidden, dtype, hops, ffn):
+    # A spin limit below 4096 makes a workgroup close a group that is not complete the moment it sits down, so most
+    # groups consist of whichever workgroups come next: the same bits, cut in two as well (the finished gates' rows then
+    # come from workgroups of other slices).
+    w = make(1_500, 200, hidden, dtype, hops, 2)
+    c = w.cfg
+    fw = synth.ffn_weights(c) if ffn else None
+    g = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops)
+    print(f"heads kernel, groups by arrival: {dtype} {hidden} hops={hops} ffn={ffn}", flush=True)
+    H = run(w, cfg_of(c, ffn=ffn), g, fw)
+    at_once = cfg_of(c, ffn=ffn, spin_limit=4095)
+    assert torch.equal(H, run(w, at_once, g, fw))
+    mid = g.n_levels // 2
+    assert torch.equal(H, run(w, at_once, g, fw, mid, None, H0=run(w, at_once, g, fw, 0, mid)))
+
+
+@pytest.mark.parametrize("hidden,dtype,n_streams", [(256, "bf16", 2), (256, "f32", 3)])
+def test_heads_kernel_on_streams_that_share_the_compute_units(hidden, dtype, n_streams):
+    # hidden 256: one workgroup fills a compute unit, and every sweep asks for all of them
+    w = make(6_000, 600, hidden, dtype, 2, 3)
+    c = w.cfg
+    g = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, 2)
+    cfg = cfg_of(c)
+    H = run(w, cfg, g)
+    X, W = to_dev(w.x, c.dtype), device_weights(w, c.dtype)
+    streams = [torch.cuda.Stream() for _ in range(n_streams)]
+    outs = [(torch.full_like(H, float("nan")), torch.empty(dg4.dg4_layer_workspace_bytes(cfg, g), dtype=torch.uint8, device="cuda"))
+            for _ in streams]
+    torch.cuda.synchronize()
+    print(f"heads kernel: {n_streams} streams, {dtype} {hidden}", flush=True)
+    for _ in range(3):
+        for s, (o, k) in zip(streams, outs):
+            with torch.cuda.stream(s):
+                dg4.dg4_layer_fwd(cfg, g, X, W, o, workspace=k)
+    torch.cuda.synchronize()
+    for o, k in outs:
+        dg4.dg4_layer_status(cfg, g, k)
+        assert torch.equal(o, H)

@@ -16,3 +16,10 @@ def compile_and_run(tmp_path, name, *args):
 def test_a_wait_gives_up_only_when_the_sweep_stands_still(tmp_path):
     r = compile_and_run(tmp_path, "wait_check")
     assert r.returncode == 0, r.stdout
+
+
+def test_groups_form_from_whichever_workgroups_run(tmp_path):
+    # with places of its XCD missing for as long as the sweep lasts, or two sweeps sharing the device, every ticket is
+    # finished by whole groups and every workgroup leaves
+    r = compile_and_run(tmp_path, "groups_check", 10)
+    assert r.returncode == 0, r.stdout
