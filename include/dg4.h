@@ -230,7 +230,10 @@ void dg4_graph_free(dg4_graph* g);
  * Bytes of device workspace the calls below need (256-byte aligned buffers).
  * dg4_layer_workspace_bytes covers dg4_layer_fwd: packed weights, the
  * projected self rows, the per-layer K/V store of finished gates and the
- * level-sorted copy of H. Negative dg4_status on a bad configuration.
+ * level-sorted copy of H. Without DG4_BOUNDED_KV the size goes by the configuration,
+ * the number of gates and the largest level, and grows with each: it is the same for
+ * every path a sweep can take (DG4_PER_LEVEL included), and what is enough for a circuit is enough
+ * for a smaller one with smaller levels. Negative dg4_status on a bad configuration.
  */
 int64_t dg4_proj_workspace_bytes(const dg4_layer_cfg* cfg);
 int64_t dg4_ffn_workspace_bytes(const dg4_layer_cfg* cfg);

@@ -56,6 +56,7 @@ constexpr int HR = DG4_HEADS_ROWS;            // most gates of a tile (one block
 // words (32 bits) of the sync area: ticket counters of the finished gates' tiles per slice, the ticket counter of
 // the sweep, the number of groups formed and of workgroups that look for another group, the words of the groups by
 // workgroup number and by order of arrival, and the (64-bit) mailboxes, every one 64 bytes from the next
+static_assert(256 / 4 <= DG4_HEADS_GROUPS, "groups of the smaller number of heads");
 constexpr int SYNC_TICKET = 8 * 16, SYNC_FORMED = 9 * 16, SYNC_LOOSE = 10 * 16, SYNC_GROUP = 11 * 16,
               SYNC_REGROUP = SYNC_GROUP + DG4_HEADS_GROUPS * 16, SYNC_MAIL = SYNC_REGROUP + DG4_HEADS_GROUPS * 16;
 static_assert((SYNC_MAIL + DG4_HEADS_GROUPS * 16) * 4 <= DG4_HEADS_SYNC_BYTES, "sync area");
@@ -983,7 +984,7 @@ int launch_heads_t(const dg4_heads_args& a, hipStream_t s)
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
     // one workgroup per compute unit, the same number for every slice
-    const int64_t per_slice = std::max<int64_t>(1, std::min<int64_t>(std::min(cus / C, DG4_HEADS_GROUPS), a.n_tiles + a.n_pre));
+    const int64_t per_slice = std::max<int64_t>(1, std::min<int64_t>(std::min(cus / C, dg4_head_groups(C)), a.n_tiles + a.n_pre));
     dg4_heads_args b = a;
     b.lanes_log2 = a.tile_rows == 2 ? 8 : a.tile_rows == 4 ? 7 : a.tile_rows == 8 ? 6 : 5;
     hipLaunchKernelGGL(kern, dim3((unsigned)(per_slice * C)), dim3(HT), smem, s, b);
@@ -992,10 +993,10 @@ int launch_heads_t(const dg4_heads_args& a, hipStream_t s)
 
 }  // namespace
 
-int64_t dg4_heads_exchange_bytes(int dtype, int hidden, bool ffn)
+int64_t dg4_heads_exchange_bytes(int dtype, int hidden, bool ffn, int64_t groups)
 {
     const int64_t es = dtype == DG4_F32 ? 4 : 2, wpr = hidden * es / 4;
-    return (int64_t)DG4_HEADS_GROUPS * HR * (2 * wpr + (ffn ? 4 * wpr + hidden : 0)) * 8;
+    return groups * HR * (2 * wpr + (ffn ? 4 * wpr + hidden : 0)) * 8;
 }
 
 int dg4_launch_heads_pack(int dtype, const dg4_heads_pack_args& a, hipStream_t s)
@@ -1008,8 +1009,9 @@ int dg4_launch_heads_pack(int dtype, const dg4_heads_pack_args& a, hipStream_t s
     return hipGetLastError();
 }
 
-int dg4_launch_heads(int dtype, int hidden, const dg4_heads_args& a, int64_t exchange_bytes, hipStream_t s)
+int dg4_launch_heads(int dtype, int hidden, const dg4_heads_args& a, hipStream_t s)
 {
+    const int64_t exchange_bytes = dg4_heads_exchange_bytes(dtype, hidden, a.ffn != 0, dg4_head_groups(hidden / 32));
     const int64_t n_flags = a.n_rows * (hidden / 32);
     const int64_t work = std::max<int64_t>(std::max(n_flags, exchange_bytes / 16), DG4_HEADS_SYNC_BYTES / 4);
     hipLaunchKernelGGL(heads_init_kernel, dim3((unsigned)std::min<int64_t>((work + 255) / 256, 2048)), dim3(256), 0, s,

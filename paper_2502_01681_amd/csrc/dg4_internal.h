@@ -328,10 +328,10 @@ struct dg4_heads_pack_args {
     void* w1_packed; void* w2_packed; int64_t ffn_layer_stride;
     float* bias_all;
 };
-int64_t dg4_heads_exchange_bytes(int dtype, int hidden, bool ffn);
+int64_t dg4_heads_exchange_bytes(int dtype, int hidden, bool ffn, int64_t groups);
 int dg4_launch_heads_pack(int dtype, const dg4_heads_pack_args& a, hipStream_t s);
 // clears flags, tickets, control words and the exchange buffer, then sweeps
-int dg4_launch_heads(int dtype, int hidden, const dg4_heads_args& a, int64_t exchange_bytes, hipStream_t s);
+int dg4_launch_heads(int dtype, int hidden, const dg4_heads_args& a, hipStream_t s);
 
 // ---- bulk projection on the matrix cores (dg4_sweep.hip): bf16, hidden 256 ----
 struct dg4_bulk_args {
