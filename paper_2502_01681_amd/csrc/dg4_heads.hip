@@ -965,12 +965,9 @@ __global__ __launch_bounds__(256) void heads_pack_kernel(dg4_heads_pack_args p)
 }
 
 template <typename T, int D>
-int launch_heads_t(const dg4_heads_args& a, hipStream_t s)
+int launch_heads_t(const dg4_heads_args& a, int64_t groups, hipStream_t s)
 {
     constexpr int C = D / 32;
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return hipErrorInvalidDevice;
     const bool wide = a.ell_w > 16;
     if (a.ell_w < 8 || a.ell_w % 4 || (!wide && a.ell_w != 8 && a.ell_w != 16)) return hipErrorInvalidValue;
     if (a.tile_rows != 2 && a.tile_rows != 4 && a.tile_rows != 8 && a.tile_rows != 16) return hipErrorInvalidValue;
@@ -983,11 +980,9 @@ int launch_heads_t(const dg4_heads_args& a, hipStream_t s)
     const size_t smem = HeadsLds<T, D, 0>::bytes(a.ell_w, a.tile_rows, a.ffn != 0);
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
-    // one workgroup per compute unit, the same number for every slice
-    const int64_t per_slice = std::max<int64_t>(1, std::min<int64_t>(std::min(cus / C, dg4_head_groups(C)), a.n_tiles + a.n_pre));
     dg4_heads_args b = a;
     b.lanes_log2 = a.tile_rows == 2 ? 8 : a.tile_rows == 4 ? 7 : a.tile_rows == 8 ? 6 : 5;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(per_slice * C)), dim3(HT), smem, s, b);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(groups * C)), dim3(HT), smem, s, b);
     return hipGetLastError();
 }
 
@@ -1011,13 +1006,19 @@ int dg4_launch_heads_pack(int dtype, const dg4_heads_pack_args& a, hipStream_t s
 
 int dg4_launch_heads(int dtype, int hidden, const dg4_heads_args& a, hipStream_t s)
 {
-    const int64_t exchange_bytes = dg4_heads_exchange_bytes(dtype, hidden, a.ffn != 0, dg4_head_groups(hidden / 32));
-    const int64_t n_flags = a.n_rows * (hidden / 32);
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return hipErrorInvalidDevice;
+    // one workgroup per compute unit, the same number for every slice; only the groups that are launched
+    // have exchange words
+    const int heads = hidden / 32;
+    const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(std::min(cus / heads, dg4_head_groups(heads)), a.n_tiles + a.n_pre));
+    const int64_t n_flags = a.n_rows * heads, exchange_bytes = dg4_heads_exchange_bytes(dtype, hidden, a.ffn != 0, groups);
     const int64_t work = std::max<int64_t>(std::max(n_flags, exchange_bytes / 16), DG4_HEADS_SYNC_BYTES / 4);
     hipLaunchKernelGGL(heads_init_kernel, dim3((unsigned)std::min<int64_t>((work + 255) / 256, 2048)), dim3(256), 0, s,
                        a.flags, n_flags, a.sync, a.ctrl, (uint4*)a.exchange, exchange_bytes / 16);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     if (a.n_tiles <= 0) return hipSuccess;
-    if (dtype == DG4_F32) return hidden == 128 ? launch_heads_t<float, 128>(a, s) : launch_heads_t<float, 256>(a, s);
-    return hidden == 128 ? launch_heads_t<bf16_t, 128>(a, s) : launch_heads_t<bf16_t, 256>(a, s);
+    if (dtype == DG4_F32) return hidden == 128 ? launch_heads_t<float, 128>(a, groups, s) : launch_heads_t<float, 256>(a, groups, s);
+    return hidden == 128 ? launch_heads_t<bf16_t, 128>(a, groups, s) : launch_heads_t<bf16_t, 256>(a, groups, s);
 }
