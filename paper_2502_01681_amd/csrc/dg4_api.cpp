@@ -378,7 +378,10 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
         const bool wide = g->ell_w > 16;
         dg4_heads_args a{};
         const int rows = dg4_heads_tile_rows(g, cfg->heads);
-        if (whole_range && !wide && dg4_levels_deeper(g) && !(cfg->flags & DG4_LEVEL_ORDER)) {
+        // (the pair table is made on first use. Shapes that no other kernel sweeps in that order know a device-built
+        // circuit's tables from dg4_graph_upload alone, also under capture: they keep the caller's levels)
+        const bool pairs_expected = dg4_flow_supports(dt, d, g->ell_w) || !g->eq1_level_ptr.empty();
+        if (whole_range && !wide && dg4_levels_deeper(g) && pairs_expected && !(cfg->flags & DG4_LEVEL_ORDER)) {
             // a caller's levelling deeper than the circuit: the dependency-driven order, its tiles (8 or 16 gates) one
             // by one or, where a level holds more than the groups, two of 8 at a time (they never depend on each other)
             rc = dg4_graph_ensure_pairs(g);

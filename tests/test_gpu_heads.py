@@ -120,6 +120,23 @@ def test_heads_kernel_under_graph_capture(hidden, dtype, hops, ffn):
     c = w.cfg
     fw = synth.ffn_weights(c) if ffn else None
     g = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops)
+    captured_sweeps(w, g, fw)
+
+
+@pytest.mark.parametrize("hidden,dtype,hops,ffn", [(256, "f32", 2, False), (128, "bf16", 3, True)])
+def test_heads_kernel_under_graph_capture_on_a_deeper_levelling(hidden, dtype, hops, ffn):
+    # ... of a graph built on the GPU under a caller's levelling: nothing to allocate there either
+    w = make(900, 90, hidden, dtype, hops, 2)
+    c = w.cfg
+    level = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops).array("level")
+    hint = np.where(level > 0, 2 * level + np.arange(c.n_nodes) % 2, 0).astype(np.int32)
+    edges = [torch.from_numpy(a).cuda() for a in (w.edge_src, w.edge_dst, w.edge_inv, hint)]
+    captured_sweeps(w, dg4.dg4_build_levels_device(c.n_nodes, *edges[:3], hops, edges[3]), synth.ffn_weights(c) if ffn else None)
+
+
+def captured_sweeps(w, g, fw):
+    c = w.cfg
+    hidden, dtype, hops, ffn = c.hidden, c.dtype, c.hops, fw is not None
     g.upload()
     cfg = cfg_of(c, ffn=ffn)
     X, W = to_dev(w.x, dtype), device_weights(w, dtype)
