@@ -744,9 +744,6 @@ int dg4_graph_ensure_pairs(dg4_graph* g)
     return DG4_OK;
 }
 
-// Device tables: fixed-width packed rows, once by node id (for calls whose
-// tensors are indexed by id) and once by position in the (level, id) order
-// (for the sweep, whose internal buffers are level sorted).
 // Runs of at most `rows` positions inside a level, as many tiles per level as a multiple of `group` (the last may be
 // empty). The caller holds g->mu.
 static int level_tiles(dg4_graph* g, int rows, int group, dg4_graph::LevelTiles& lt)
@@ -794,12 +791,37 @@ int dg4_graph_ensure_level_pairs(dg4_graph* g, const dg4_graph::LevelTiles** out
     return level_tiles(g, DG4_TILE_ROWS, 2, g->level_pairs);
 }
 
+// The number of Eq. 1 levels of a graph built on the GPU under a deeper levelling: one pass over the fanins, in the order of
+// that levelling. The caller holds g->mu.
+static int find_own_depth(dg4_graph* g)
+{
+    if (g->fanin.empty()) return DG4_OK;
+    try {
+        std::vector<int32_t> own((size_t)g->n, 0);
+        int32_t deepest = 0;
+        for (const int32_t v : g->order) {
+            for (int k = 0; k < 2; ++k)
+                if (const int32_t u = g->fanin[2 * (size_t)v + k]; u >= 0) own[v] = std::max(own[v], own[u] + 1);
+            deepest = std::max(deepest, own[v]);
+        }
+        g->own_depth = (int64_t)deepest + 1;
+        std::vector<int32_t>().swap(g->fanin);
+    } catch (const std::bad_alloc&) {
+        return DG4_ENOMEM;
+    }
+    return DG4_OK;
+}
+
+// Device tables: fixed-width packed rows, once by node id (for calls whose
+// tensors are indexed by id) and once by position in the (level, id) order
+// (for the sweep, whose internal buffers are level sorted).
 int dg4_graph_ensure_device(dg4_graph* g)
 {
     std::lock_guard<std::mutex> lock(g->mu);
     if (g->on_device) return DG4_OK;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return DG4_EHIP;
+    if (const int rc = find_own_depth(g); rc != DG4_OK) return rc;
     // (one-hop cones get rows of 8 as well: the persistent sweep is laid out for that width; cones
     // deeper than three hops get the longest row, rounded up to four entries)
     int w = std::max(8, 1 << (std::min(g->hops, 3) + 1));

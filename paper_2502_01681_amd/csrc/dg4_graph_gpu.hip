@@ -86,15 +86,20 @@ __global__ __launch_bounds__(256) void level_round_kernel(int64_t n, const int32
 }
 
 // a caller's levelling: non-negative, 0 exactly on primary inputs' side of the rule, strictly
-// increasing along every edge (which also rules out cycles)
-__global__ void hint_check_kernel(int64_t n, const int32_t* fin, const int32_t* deg, const int32_t* hint, int32_t* level, int* status)
+// increasing along every edge (which also rules out cycles). deeper: some gate lies above its Eq. 1 level's place (one
+// past its latest fanin). Slots of the fanin table without a fanin become -1.
+__global__ void hint_check_kernel(int64_t n, int32_t* fin, const int32_t* deg, const int32_t* hint, int32_t* level, int* deeper, int* status)
 {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= n) return;
     const int32_t h = hint[v];
     bool ok = h >= 0 && !(deg[v] == 0 && h != 0);
-    for (int k = 0; k < deg[v]; ++k) ok = ok && hint[fin[2 * v + k]] < h;
+    int32_t latest = -1;
+    for (int k = 0; k < deg[v]; ++k) latest = max(latest, hint[fin[2 * v + k]]);
+    for (int k = deg[v]; k < 2; ++k) fin[2 * v + k] = -1;
+    ok = ok && (deg[v] == 0 || latest < h);
     if (!ok) report(status, DG4_EHINT);
+    if (deg[v] > 0 && h > latest + 1) *deeper = 1;
     level[v] = h;
 }
 
@@ -601,26 +606,31 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
         GPU_CHECK(hipStreamSynchronize(s));
         if (st != DG4_OK) return st;
 
-        int32_t* hinted = nullptr;
         if (level_hint) {
-            hinted = arena.get<int32_t>((size_t)n, false, s);
-            if (!hinted) return DG4_ENOMEM;
-            hipLaunchKernelGGL(hint_check_kernel, dim3(nb), dim3(256), 0, s, n, fin, deg, level_hint, hinted, status);
+            GPU_ALLOC(deeper, int, 1, true);
+            hipLaunchKernelGGL(hint_check_kernel, dim3(nb), dim3(256), 0, s, n, fin, deg, level_hint, level, deeper, status);
+            int is_deeper = 0;
             GPU_CHECK(hipMemcpyAsync(&st, status, sizeof(int), hipMemcpyDeviceToHost, s));
+            GPU_CHECK(hipMemcpyAsync(&is_deeper, deeper, sizeof(int), hipMemcpyDeviceToHost, s));
             GPU_CHECK(hipStreamSynchronize(s));
             if (st != DG4_OK) return st;
-        }
-        // launches of Eq. 1 rounds, a batch at a time; no progress in a batch with gates left = a cycle (with a
-        // caller's levelling only their depth is used: which kernel sweeps the graph goes by it)
-        unsigned long long finished = 0, before = ~0ull;
-        for (;;) {
-            GPU_CHECK(hipMemcpyAsync(&finished, progress, sizeof(finished), hipMemcpyDeviceToHost, s));
-            GPU_CHECK(hipStreamSynchronize(s));
-            if (finished == (unsigned long long)n) break;
-            if (finished == before) return DG4_ECYCLE;
-            before = finished;
-            for (int r = 0; r < 2; ++r)
-                hipLaunchKernelGGL(level_round_kernel, dim3(nb), dim3(256), 0, s, n, fin, deg, level, progress);
+            // (which kernel sweeps the graph goes by the circuit's own depth: found from these on the first device call)
+            if (is_deeper) {
+                g->fanin.resize(2 * (size_t)n);
+                GPU_CHECK(hipMemcpyAsync(g->fanin.data(), fin, 2 * (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+            }
+        } else {
+            // launches of Eq. 1 rounds, a batch at a time; no progress in a batch with gates left = a cycle
+            unsigned long long finished = 0, before = ~0ull;
+            for (;;) {
+                GPU_CHECK(hipMemcpyAsync(&finished, progress, sizeof(finished), hipMemcpyDeviceToHost, s));
+                GPU_CHECK(hipStreamSynchronize(s));
+                if (finished == (unsigned long long)n) break;
+                if (finished == before) return DG4_ECYCLE;
+                before = finished;
+                for (int r = 0; r < 2; ++r)
+                    hipLaunchKernelGGL(level_round_kernel, dim3(nb), dim3(256), 0, s, n, fin, deg, level, progress);
+            }
         }
 
         // (level, id) order: stable sort of the ids by level
@@ -628,14 +638,6 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
         GPU_ALLOC(sorted_level, int32_t, (size_t)n, false);
         GPU_ALLOC(order, int32_t, (size_t)n, false);
         int32_t h_max = 0;
-        if (hinted) {
-            GPU_ALLOC(own_max, int32_t, 1, true);
-            hipLaunchKernelGGL(iota_max_kernel, dim3(nb), dim3(256), 0, s, n, level, ids, own_max);
-            GPU_CHECK(hipMemcpyAsync(&h_max, own_max, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-            GPU_CHECK(hipStreamSynchronize(s));
-            g->own_depth = h_max + 1;
-            level = hinted;
-        }
         hipLaunchKernelGGL(iota_max_kernel, dim3(nb), dim3(256), 0, s, n, level, ids, max_level);
         GPU_CHECK(hipMemcpyAsync(&h_max, max_level, sizeof(int32_t), hipMemcpyDeviceToHost, s));
         GPU_CHECK(hipStreamSynchronize(s));

@@ -40,7 +40,10 @@ struct dg4_graph {
     // Partitioned graphs (dg4_build_partitioned): Algorithm 1's lists; with marks the mini-batch of
     // each gate; without marks the nodes are copies: the gate each stands for, each gate's last copy.
     int32_t stride = 0, batch_cones = 0;
-    int64_t own_depth = 0;                       // built on the GPU with a caller's levelling: the number of Eq. 1 levels
+    // Built on the GPU under a caller's levelling deeper than Eq. 1: the fanins (two per gate, -1: none), from which the first
+    // device call finds the number of Eq. 1 levels.
+    std::vector<int32_t> fanin;
+    int64_t own_depth = 0;
     bool marks = true;
     std::vector<int32_t> cone_root, cone_group_level, stage;
     std::vector<int64_t> cone_group_ptr;
@@ -105,7 +108,8 @@ struct dg4_graph {
     int pair_tile_rows = 0;          // gates of its largest tile
 };
 
-// Levels of the dependencies a whole sweep follows (Eq. 1), whether the graph's own levelling is deeper, gates per level
+// Levels of the dependencies a whole sweep follows (Eq. 1), whether the graph's own levelling is deeper, gates per level:
+// after dg4_graph_ensure_device
 inline int64_t dg4_dependency_depth(const dg4_graph* g)
 {
     if (!g->eq1_level_ptr.empty()) return (int64_t)g->eq1_level_ptr.size() - 1;

@@ -202,6 +202,26 @@ def test_path_goes_by_the_circuits_own_depth():
     assert torch.equal(H, run(w, cfg, dg4.dg4_build_levels_device(c.n_nodes, *edges, 2, torch.from_numpy(hint).cuda())))
 
 
+def test_path_goes_by_the_circuits_own_depth_with_one_fanin_gates():
+    # ... where some gates have one fanin, and where a device-built graph's levelling is the circuit's own one
+    w = synth.make(synth.Config("flat", 78, 500, 9_000, 4_000, 0.5, 3, 128, 4, 2, 2, "f32"))
+    c = w.cfg
+    cfg = cfg_of(c)
+    keep = np.ones(len(w.edge_src), dtype=bool)
+    keep[1::6] = False                      # every third gate keeps one of its two fanins
+    host = [np.ascontiguousarray(a[keep]) for a in (w.edge_src, w.edge_dst, w.edge_inv)]
+    g = dg4.dg4_build_levels(c.n_nodes, *host, 2)
+    level = g.array("level")
+    H = run(w, cfg, g)
+    edges = [torch.from_numpy(a).cuda() for a in host]
+    for hint in (level, np.where(level > 0, 200 * level + np.arange(c.n_nodes) % 150, 0)):
+        hint = np.ascontiguousarray(hint.astype(np.int32))
+        on_gpu = dg4.dg4_build_levels_device(c.n_nodes, *edges, 2, torch.from_numpy(hint).cuda())
+        assert np.array_equal(on_gpu.array("level"), hint)
+        assert torch.equal(H, run(w, cfg, on_gpu))
+        assert torch.equal(H, run(w, cfg, dg4.dg4_build_levels(c.n_nodes, *host, 2, hint)))
+
+
 @pytest.mark.parametrize("hidden,dtype,hops,ffn", [(256, "bf16", 2, False), (128, "f32", 3, False), (256, "f32", 2, True), (128, "bf16", 5, False)])
 def test_heads_kernel_in_groups_by_order_of_arrival(hidden, dtype, hops, ffn):
     # A spin limit below 4096 makes a workgroup close a group that is not complete the moment it sits down, so most
