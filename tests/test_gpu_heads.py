@@ -34,11 +34,11 @@ def run(w, cfg, g, ffn=None, level_begin=0, level_end=None, H0=None):
 @pytest.mark.parametrize("n_and,window,hops,layers,ffn", [
     (3, 2, 1, 2, False),                    # fewer gates than a tile, fewer tiles than groups
     (700, 60, 2, 2, False), (700, 60, 3, 1, False),
-    (2_500, 2_400, 2, 2, False),            # a few hundred gates per level: two tiles of 8 at a time
+    (2_500, 2_400, 2, 2, False),            # a hundred gates per level: tiles of two (hidden 128) and four
     (600, 60, 2, 2, True),
     (500, 20, 5, 2, False),                 # wide rows, tiles of two gates (16 lane groups and more per gate)
-    (1_500, 900, 5, 1, False),              # tiles of four and eight
-    (4_000, 3_900, 4, 2, False),            # tiles of sixteen
+    (1_500, 900, 5, 1, False),              # ... of two
+    (4_000, 3_900, 4, 2, False),            # ... of four (hidden 128) and eight
     (900, 300, 6, 2, True),
 ])
 def test_heads_kernel_against_oracle(hidden, dtype, n_and, window, hops, layers, ffn):
@@ -163,7 +163,7 @@ def captured_sweeps(w, g, fw):
 
 @pytest.mark.parametrize("hidden,dtype,n_and,window,hops,ffn", [
     (128, "f32", 900, 90, 2, False),        # a handful of gates per level: the list schedule's tiles one by one
-    (256, "bf16", 4_000, 3_000, 3, True),   # more than a round of its tiles of 8: two at a time
+    (256, "bf16", 4_000, 3_000, 3, True),   # a round of its tiles of 8
     (128, "bf16", 700, 60, 5, False),       # wide rows: tiles cut from the caller's levels
 ])
 def test_heads_kernel_on_a_deeper_levelling(hidden, dtype, n_and, window, hops, ffn):
@@ -261,3 +261,73 @@ def test_heads_kernel_on_streams_that_share_the_compute_units(hidden, dtype, n_s
     for o, k in outs:
         dg4.dg4_layer_status(cfg, g, k)
         assert torch.equal(o, H)
+
+
+def shape_of(w, levels, ffn):
+    """What the rules make of a circuit with this many (Eq. 1) levels: whether it takes the heads kernel, gates per tile."""
+    c = w.cfg
+    groups, width = 256 // c.heads, c.n_nodes // levels
+    streamed = (c.dtype, c.hidden) in (("f32", 128), ("bf16", 256)) and (not ffn or c.hops <= 3)
+    rows = 2
+    while rows < 16 and 4 * width > 5 * groups * rows:
+        rows *= 2
+    return width <= groups * 16 * (4 if not streamed else 2 if c.hops >= 6 else 1), rows
+
+
+def make_flat(n_pi, n_and, cap, hidden, dtype, hops, layers):
+    return synth.make(synth.Config("heads", 79, n_pi, n_and, 2_000, 0.5, cap, hidden, hidden // 32, hops, layers, dtype))
+
+
+@pytest.mark.parametrize("hidden,dtype,n_pi,n_and,cap,hops,layers,ffn,rows", [
+    (256, "bf16", 400, 2_000, 14, 2, 2, False, 16), (128, "f32", 400, 6_000, 8, 3, 2, False, 16),
+    (256, "bf16", 400, 2_000, 14, 4, 2, False, 16), (256, "f32", 400, 2_000, 14, 4, 1, False, 16),
+    (128, "f32", 400, 6_000, 8, 4, 2, False, 16), (128, "bf16", 400, 6_000, 8, 5, 1, False, 16),
+    (256, "bf16", 400, 2_000, 14, 5, 2, True, 16), (256, "f32", 400, 2_000, 14, 4, 2, True, 16),
+    (128, "f32", 400, 6_000, 8, 4, 1, True, 16), (128, "bf16", 400, 6_000, 8, 4, 2, True, 16),
+    (128, "f32", 400, 3_500, 8, 5, 2, False, 8), (256, "bf16", 150, 1_400, 9, 5, 2, False, 8), (256, "f32", 150, 1_400, 9, 6, 1, True, 8),
+    (128, "bf16", 150, 1_400, 9, 4, 2, True, 4), (256, "f32", 60, 700, 9, 6, 2, False, 4),
+])
+def test_heads_kernel_with_every_tile_size_on_wide_rows(hidden, dtype, n_pi, n_and, cap, hops, layers, ffn, rows):
+    w = make_flat(n_pi, n_and, cap, hidden, dtype, hops, layers)
+    c = w.cfg
+    fw = synth.ffn_weights(c) if ffn else None
+    g = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops)
+    assert shape_of(w, g.n_levels, ffn) == (True, rows)
+    print(f"heads kernel, tiles of {rows}: {dtype} {hidden} {c.n_nodes // g.n_levels} gates per level hops={hops} ffn={ffn}", flush=True)
+    cfg = cfg_of(c, ffn=ffn)
+    H = run(w, cfg, g, fw)
+    og = oracle.build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops)
+    assert (int(np.diff(og.nbr_ptr).max()) > 16) == (hops > 3)
+    kw = dict(w1=fw[0], w2=fw[1]) if ffn else {}
+    ref = oracle.layer_fwd(og, w.x, w.wqkv, w.wo, w.rel_bias, c.heads, store=dtype, **kw)
+    assert row_rel_err(to_np(H), ref).max() <= TOL[dtype]
+    mid = g.n_levels // 2
+    assert torch.equal(H, run(w, cfg, g, fw, mid, None, H0=run(w, cfg, g, fw, 0, mid)))
+
+
+@pytest.mark.parametrize("hidden,dtype,n_pi,n_and,cap,hops,ffn", [
+    (256, "bf16", 400, 2_000, 14, 2, False), (256, "bf16", 400, 2_000, 14, 3, True),
+    (128, "f32", 400, 6_000, 8, 3, False), (128, "f32", 400, 6_000, 8, 2, True),
+])
+def test_heads_kernel_takes_two_tiles_of_the_pair_table_at_a_time(hidden, dtype, n_pi, n_and, cap, hops, ffn):
+    # a deeper levelling of a circuit whose levels hold more than one round of the table's tiles of 8
+    w = make_flat(n_pi, n_and, cap, hidden, dtype, hops, 2)
+    c = w.cfg
+    fw = synth.ffn_weights(c) if ffn else None
+    cfg = cfg_of(c, ffn=ffn)
+    g = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops)
+    level = g.array("level")
+    hint = np.where(level > 0, 2 * level + np.arange(c.n_nodes) % 2, 0).astype(np.int32)
+    deeper = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops, hint)
+    assert deeper.n_levels > g.n_levels and shape_of(w, g.n_levels, ffn) == (True, 16)
+    tiles = np.diff(deeper.array("pair_tile_ptr"))
+    assert tiles.max() == 8 and tiles.min() >= 0
+    print(f"heads kernel, two tiles of 8: {dtype} {hidden} {c.n_nodes // g.n_levels} gates per level hops={hops} ffn={ffn}", flush=True)
+    H = run(w, cfg, g, fw)
+    og = oracle.build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops)
+    kw = dict(w1=fw[0], w2=fw[1]) if ffn else {}
+    ref = oracle.layer_fwd(og, w.x, w.wqkv, w.wo, w.rel_bias, c.heads, store=dtype, **kw)
+    assert row_rel_err(to_np(H), ref).max() <= TOL[dtype]
+    assert torch.equal(H, run(w, cfg, deeper, fw))
+    edges = [torch.from_numpy(a).cuda() for a in (w.edge_src, w.edge_dst, w.edge_inv, hint)]
+    assert torch.equal(H, run(w, cfg, dg4.dg4_build_levels_device(c.n_nodes, *edges[:3], hops, edges[3]), fw))
