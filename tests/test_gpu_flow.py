@@ -1,6 +1,8 @@
 """The persistent dataflow kernel for every shape (fp32 / hidden 128, bf16 / hidden 256, cones of up to
 three hops, any number of layers) against the oracle, against level-by-level launches (other kernels,
 another summation order: equal up to rounding) and, bit for bit, against itself under other schedules.
+Circuits with few gates per level are swept by the kernel that spreads heads over compute units, so of the cases below the
+named narrow ones ("tiny", "small", "medium") run that one; the cases on `flat` circuits state their gates per level.
 """
 import numpy as np
 import pytest
@@ -26,6 +28,18 @@ def graphs(w, hint=True):
     g = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, c.hops, h)
     og = oracle.build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, c.hops, h)
     return g, og
+
+
+def flat(n_and, dtype, hops, layers, ffn=False):
+    """A wide circuit (six to nine levels), and the check that it lies above the line to the other kernel."""
+    hidden = 128 if dtype == "f32" else 256
+    w = synth.make(synth.Config("flat", 80, 400, n_and, 2_000, 0.5, 8, hidden, hidden // 32, hops, layers, dtype))
+    g, _ = graphs(w, hint=False)
+    gates_per_level = w.cfg.n_nodes // g.n_levels
+    assert gates_per_level > 256 // w.cfg.heads * 16 * (2 if hops >= 6 else 1)
+    assert not ffn or hops <= 3                    # (deeper cones with the feed-forward sub-block go level by level there)
+    print(f"flat circuit {dtype}: {w.cfg.n_nodes} gates, {gates_per_level} per level, hops={hops} layers={layers} ffn={ffn}", flush=True)
+    return w
 
 
 def run(w, cfg, g, level_begin=0, level_end=None, H0=None, poison=False):
@@ -69,7 +83,14 @@ def test_flow_kernel_against_oracle_and_level_by_level(name, n_and, over):
 
 
 def test_flow_kernel_without_epilogue():
-    w = make("tiny")
+    without_epilogue(make("tiny"))
+
+
+def test_flow_kernel_without_epilogue_on_a_flat_circuit():
+    without_epilogue(flat(9_000, "f32", 2, 1))
+
+
+def without_epilogue(w):
     g, og = graphs(w)
     cfg = cfg_of(w.cfg, epilogue=False)
     H = run(w, cfg, g)
@@ -107,7 +128,15 @@ def test_flow_kernel_bounded_wait_and_packed_weights(n_layers):
     # narrow circuit: also on a source whose later layers are not in the store yet): the sweep must return,
     # report it, publish nothing more of the abandoned tile, and a normal run afterwards is correct. Then
     # the packed weights of that run serve a third one.
-    w = make("small", n_layers=n_layers)
+    bounded_wait(make("small", n_layers=n_layers))
+
+
+@pytest.mark.parametrize("dtype,n_and,hops,layers", [("f32", 12_000, 2, 1), ("f32", 12_000, 2, 3), ("bf16", 8_000, 3, 2), ("f32", 16_000, 5, 2)])
+def test_flow_kernel_bounded_wait_and_packed_weights_on_flat_circuits(dtype, n_and, hops, layers):
+    bounded_wait(flat(n_and, dtype, hops, layers))
+
+
+def bounded_wait(w):
     c = w.cfg
     g, og = graphs(w)
     X, W = to_dev(w.x, c.dtype), device_weights(w, c.dtype)
@@ -138,7 +167,16 @@ def test_flow_kernel_on_wide_rows(name, n_and, k, over):
     # cones deeper than three hops (rows of up to 2^(k+1)-1 sources, several lane groups per gate):
     # against the oracle, against level-by-level launches, and bit for bit against a sweep cut in two
     print(f"flow kernel, wide rows {name} n_and={n_and} k={k} {over}", flush=True)
-    w = make(name, n_and, hops=k, **over)
+    wide_rows(make(name, n_and, hops=k, **over))
+
+
+@pytest.mark.parametrize("dtype,n_and,k,layers", [("f32", 16_000, 4, 2), ("f32", 16_000, 5, 1), ("f32", 24_000, 8, 1),
+                                                  ("bf16", 6_000, 5, 2), ("bf16", 12_000, 6, 1)])
+def test_flow_kernel_on_wide_rows_of_flat_circuits(dtype, n_and, k, layers):
+    wide_rows(flat(n_and, dtype, k, layers))
+
+
+def wide_rows(w):
     c = w.cfg
     g, og = graphs(w)
     assert int(np.diff(og.nbr_ptr).max()) > 16
@@ -165,7 +203,15 @@ def test_flow_kernel_with_feed_forward(name, n_and, over):
     # the whole transformer block per layer (attention sub-block, then LN(h + relu(h W1) W2)), up to the
     # paper's twelve layers, in one persistent launch
     print(f"flow kernel + feed-forward {name} n_and={n_and} {over}", flush=True)
-    w = make(name, n_and, **over)
+    with_feed_forward(make(name, n_and, **over))
+
+
+@pytest.mark.parametrize("dtype,n_and,hops,layers", [("f32", 12_000, 2, 1), ("f32", 9_000, 3, 2), ("bf16", 6_000, 3, 1), ("bf16", 9_000, 2, 3)])
+def test_flow_kernel_with_feed_forward_on_flat_circuits(dtype, n_and, hops, layers):
+    with_feed_forward(flat(n_and, dtype, hops, layers, ffn=True))
+
+
+def with_feed_forward(w):
     c = w.cfg
     w1, w2 = synth.ffn_weights(c)
     g, og = graphs(w)
