@@ -546,27 +546,30 @@ __global__ void position_kernel(int64_t n, const int32_t* order, int32_t* pos)
     if (r < n) pos[order[r]] = (int32_t)r;
 }
 
-// One fixed-width table of packed neighbour rows: row r holds the row of node order[r] (null: r), entries by position
-// (null: by id) in ascending-id order, padded. Four entries per thread; bound by the table's own bytes and, by
-// position, the gather of the positions.
-__global__ __launch_bounds__(256) void pack_rows_kernel(int64_t n, int64_t rows, int w4, const int64_t* ptr, const int32_t* idx,
-                                                        const uint8_t* rel, const int32_t* order, const int32_t* pos, uint4* table)
+// Packed neighbour rows of nodes v0 .. v0 + count - 1 in a fixed-width table: a node's row at its position (pos null:
+// at its id), entries by position (by id) in ascending-id order, padded. ptr, idx, rel: these nodes' part of the CSR;
+// first: the entry idx begins with; pad: empty rows behind position v0 + count. Four entries per thread; bound by the
+// table's own bytes and, by position, the gather of the positions.
+__global__ __launch_bounds__(256) void pack_rows_kernel(int64_t v0, int64_t count, int64_t pad, int w4, const int64_t* ptr, int64_t first,
+                                                        const int32_t* idx, const uint8_t* rel, const int32_t* pos, uint4* table)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= rows * w4) return;
-    const int64_t r = i / w4;
+    if (i >= (count + pad) * w4) return;
+    const int64_t k = i / w4;
+    if (k >= count) {
+        table[v0 * w4 + i] = make_uint4(DG4_ELL_PAD, DG4_ELL_PAD, DG4_ELL_PAD, DG4_ELL_PAD);
+        return;
+    }
+    const int64_t lo = ptr[k] - first, cnt = ptr[k + 1] - ptr[k];
     const int j0 = (int)(i % w4) * 4;
     uint32_t e[4] = { DG4_ELL_PAD, DG4_ELL_PAD, DG4_ELL_PAD, DG4_ELL_PAD };
-    if (r < n) {
-        const int64_t v = order ? order[r] : r, lo = ptr[v], cnt = ptr[v + 1] - lo;
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (j0 + q < cnt) {
-                const int32_t u = idx[lo + j0 + q];
-                e[q] = (uint32_t)rel[lo + j0 + q] << 30 | (uint32_t)(pos ? pos[u] : u);
-            }
-    }
-    table[i] = make_uint4(e[0], e[1], e[2], e[3]);
+    for (int q = 0; q < 4; ++q)
+        if (j0 + q < cnt) {
+            const int32_t u = idx[lo + j0 + q];
+            e[q] = (uint32_t)rel[lo + j0 + q] << 30 | (uint32_t)(pos ? pos[u] : u);
+        }
+    table[(pos ? pos[v0 + k] : v0 + k) * w4 + i % w4] = make_uint4(e[0], e[1], e[2], e[3]);
 }
 
 // stride == 0: plain cone rows; else the rows of the partitioned update with marks
@@ -811,29 +814,49 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
 }  // namespace
 
 // The neighbour rows of g (host CSR) as `count` tables of rows x w entries on the current device, table i in the order
-// d_orders[i] (device, null: by node id). Synchronous, like the copies around it; temporary device memory of 12 bytes
-// per node and 5 per neighbour entry.
+// d_orders[i] (device, null: by node id). Synchronous, like the copies around it. The CSR crosses in pieces of at
+// most PACK_NODES nodes and about PACK_ENTRIES entries, so that next to the tables there are never more than 176 MB and,
+// per ordered table, four bytes per node (the whole CSR at once would be up to five eighths of a table: 460 MB at 92 M
+// entries; upload 6.1 to 7 ms for 101 K gates and 125 to 150 ms for 201 K of 456 entries either way).
+constexpr int64_t PACK_NODES = 1 << 20, PACK_ENTRIES = 1 << 25;
 int dg4_pack_rows(const dg4_graph* g, int w, int64_t rows, int count, const int32_t* const* d_orders, uint32_t* const* d_tables)
 {
-    if (w <= 0 || w % 4 || rows < g->n) return DG4_EINVAL;
+    if (w <= 0 || w % 4 || rows < g->n || count > 3) return DG4_EINVAL;
     hipStream_t s = nullptr;
-    const size_t n = (size_t)g->n, nnz = (size_t)g->nnz;
+    const int64_t n = g->n, w4 = w / 4;
     Arena arena;
-    if (!arena.reserve((n + 1) * 8 + nnz * 5 + n * 4 + 4096)) return DG4_ENOMEM;
-    GPU_ALLOC(ptr, int64_t, n + 1, false);
-    GPU_ALLOC(idx, int32_t, nnz, false);
-    GPU_ALLOC(rel, uint8_t, nnz, false);
-    GPU_ALLOC(pos, int32_t, n, false);
-    GPU_CHECK(hipMemcpy(ptr, g->nbr_ptr.data(), (n + 1) * 8, hipMemcpyHostToDevice));
-    if (nnz) {
-        GPU_CHECK(hipMemcpy(idx, g->nbr_idx.data(), nnz * 4, hipMemcpyHostToDevice));
-        GPU_CHECK(hipMemcpy(rel, g->nbr_rel.data(), nnz, hipMemcpyHostToDevice));
-    }
+    int32_t* pos[3] = {};
+    int ordered = 0;
+    for (int t = 0; t < count; ++t) ordered += d_orders[t] != nullptr;
+    const size_t most = (size_t)std::min(g->nnz, PACK_ENTRIES + w), most_nodes = (size_t)std::min(n, PACK_NODES);
+    if (!arena.reserve((most_nodes + 1) * 8 + most * 5 + (size_t)ordered * (size_t)n * 4 + 8192)) return DG4_ENOMEM;
+    GPU_ALLOC(ptr, int64_t, most_nodes + 1, false);
+    GPU_ALLOC(idx, int32_t, most, false);
+    GPU_ALLOC(rel, uint8_t, most, false);
     for (int t = 0; t < count; ++t) {
-        if (d_orders[t] && n) hipLaunchKernelGGL(position_kernel, dim3(blocks_for(g->n)), dim3(256), 0, s, g->n, d_orders[t], pos);
-        hipLaunchKernelGGL(pack_rows_kernel, dim3(blocks_for(rows * (w / 4))), dim3(256), 0, s, g->n, rows, w / 4, ptr, idx, rel,
-                           d_orders[t], d_orders[t] ? (const int32_t*)pos : (const int32_t*)nullptr, (uint4*)d_tables[t]);
+        if (d_orders[t] && n) {
+            if (!(pos[t] = arena.get<int32_t>((size_t)n, false, s))) return DG4_ENOMEM;
+            hipLaunchKernelGGL(position_kernel, dim3(blocks_for(n)), dim3(256), 0, s, n, d_orders[t], pos[t]);
+        }
     }
+    int64_t v0 = 0, v1 = 0;
+    do {
+        v0 = v1;
+        const int64_t first = g->nbr_ptr[(size_t)v0];
+        // (a row holds at most w entries)
+        while (v1 < n && v1 - v0 < PACK_NODES && g->nbr_ptr[(size_t)v1] - first < PACK_ENTRIES) ++v1;
+        const int64_t entries = g->nbr_ptr[(size_t)v1] - first;
+        if (entries > (int64_t)most) return DG4_EINVAL;
+        GPU_CHECK(hipMemcpy(ptr, g->nbr_ptr.data() + v0, (size_t)(v1 - v0 + 1) * 8, hipMemcpyHostToDevice));
+        if (entries) {
+            GPU_CHECK(hipMemcpy(idx, g->nbr_idx.data() + first, (size_t)entries * 4, hipMemcpyHostToDevice));
+            GPU_CHECK(hipMemcpy(rel, g->nbr_rel.data() + first, (size_t)entries, hipMemcpyHostToDevice));
+        }
+        const int64_t pad = v1 == n ? rows - n : 0;
+        for (int t = 0; t < count; ++t)
+            hipLaunchKernelGGL(pack_rows_kernel, dim3(blocks_for((v1 - v0 + pad) * w4)), dim3(256), 0, s, v0, v1 - v0, pad, (int)w4, ptr, first,
+                               idx, rel, (const int32_t*)pos[t], (uint4*)d_tables[t]);
+    } while (v1 < n);
     GPU_CHECK(hipGetLastError());
     GPU_CHECK(hipStreamSynchronize(s));
     return DG4_OK;
