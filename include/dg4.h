@@ -72,8 +72,8 @@ typedef enum {
                             /* levels (the caller's level_hint, if one was given) instead of  */
                             /* the library's dependency-driven order. Same results bit for    */
                             /* bit; for comparisons of schedules                              */
-#define DG4_PROFILE     32u /* dg4_layer_fwd: the specialised persistent kernel accumulates    */
-                            /* per-phase timers, read back by dg4_layer_profile                */
+#define DG4_PROFILE     32u /* dg4_layer_fwd: the persistent kernel accumulates per-phase      */
+                            /* timers, read back by dg4_layer_profile                          */
 #define DG4_TIME_SWEEP  64u /* dg4_layer_fwd: bracket the persistent kernel with two events on  */
                             /* the caller's stream, read back by dg4_sweep_elapsed_ms           */
 #define DG4_WEIGHTS_PACKED 128u /* dg4_layer_fwd: the caller vouches that W holds the same      */
@@ -354,8 +354,15 @@ int dg4_layer_status(const dg4_layer_cfg* cfg, const dg4_graph* g, const void* w
  * and graph, after the caller synchronised the stream) the abort flag of the
  * kernel's bounded dependency wait (0 = the sweep ran to completion) and, if
  * DG4_PROFILE was set in that call's cfg->flags, eight
- * per-phase timers in 10 ns ticks summed over workgroups: tiles with a late source (a count), dependency
- * wait, attention, output projection, LayerNorm, K|V projection, publish, feed-forward sub-block.
+ * per-phase timers in 10 ns ticks summed over workgroups, those of the kernel that ran:
+ *   weights in registers (bf16, hidden 256, one layer, hops <= 2): tiles with a late source (a count), dependency wait,
+ *     attention, output projection, LayerNorm, K|V projection, publish, feed-forward sub-block;
+ *   heads of a tile spread over compute units (few gates per level): ticket, first projection and dependency wait,
+ *     attention with its exchange, output projection and LayerNorm, Q|K|V of the next layer, rows out and K|V
+ *     projection, publish, feed-forward sub-block with its exchanges;
+ *   weights streamed (wide circuits): ticket, dependency wait, attention, output projection and LayerNorm, Q|K|V of the
+ *     next layer, rows out and K|V projection, publish, and, with DG4_FFN, output projection to feed-forward sub-block
+ *     in place of the fourth.
  */
 int dg4_layer_profile(const dg4_layer_cfg* cfg, const dg4_graph* g, const void* workspace,
                       uint64_t* ticks8, uint32_t* aborted);

@@ -59,7 +59,7 @@ class LayerConfig:
     bounded_kv: bool = False     # no K|V store: one level's frontier is projected when the level is processed
     ffn: bool = False            # every layer ends with the feed-forward sub-block (weights W1, W2 per layer)
     level_order: bool = False    # whole-graph sweeps follow the graph's own levels, not the dependency-driven order
-    profile: bool = False        # phase timers of the specialised persistent kernel (dg4_layer_profile)
+    profile: bool = False        # phase timers of the persistent kernel (dg4_layer_profile)
     time_sweep: bool = False     # events around the persistent kernel (dg4_sweep_elapsed_ms)
     weights_packed: bool = False # reuse the packed weights the previous call left in the workspace
     spin_limit: int = 0          # polls before a persistent sweep gives up on a dependency (0: default)

@@ -72,11 +72,14 @@ bool heads_config(const dg4_layer_cfg* c)
 // handing whole tiles to compute units wastes less. Measured, time of the other path over this one, against gates
 // per level. fp32 / 128, two hops: 1.33 at 217, 1.35 at 732, 0.94 at 1172 (four layers 1.34, 1.30, 1.01; with
 // feed-forward 1.38, 1.20, 0.92); bf16 / 256, four layers: 1.48 at 217, 1.49 at 387, 0.92 at 732; three hops 1.29,
-// 1.31, 0.77. Cones of six hops and more are bound by the gathers, of which this kernel makes fewer from memory:
-// 1.47 at 1314 and 1.62 at 3038 (fp32 / 128), 1.11 and 1.18 (bf16 / 256), so twice the line (at five hops 1.03
-// at 1314, 1.05 at 778). Where the other path is level-by-level launches (bf16 / 128, fp32 / 256, feed-forward
-// on cones of more than three hops), four times: bf16 / 128 5.5 at 217, 2.5 at 1640, 0.79 at 6780; fp32 / 256 6.7,
-// 1.8, 0.69. One layer over two hops in bf16 / 256 without feed-forward has a kernel of its own.
+// 1.31, 0.77. Five hops stay on this line, though both shapes were measured slightly ahead above it (fp32 / 128 1.03 and
+// 1.15 with two layers at 1314, bf16 / 256 1.11 at 657 and 1.05 at 778). Cones of six hops and more are bound by the
+// gathers, of which this kernel makes fewer from memory: 1.47 at 1314 and 1.62 at 3038 (fp32 / 128), 1.11 and 1.18
+// (bf16 / 256). There the line is twice as high, which is no crossing: the kernel is still ahead at 3038, the widest
+// that was measured, and up to there wider circuits give that away. Where the other path is level-by-level launches
+// (bf16 / 128, fp32 / 256, feed-forward on cones of more than three hops), four times: bf16 / 128 5.5 at 217, 2.5
+// at 1640, 0.79 at 6780; fp32 / 256 6.7, 1.8, 0.69. One layer over two hops in bf16 / 256 without feed-forward has
+// a kernel of its own.
 bool heads_route(const dg4_layer_cfg* c, const dg4_graph* g)
 {
     // (without marks the nodes are copies in many shallow components: never narrow)

@@ -207,7 +207,8 @@ __global__ __launch_bounds__(FLOW_THREADS) void flow_kernel(dg4_flow_args p)
     const int L = p.n_layers;
 
     // optional phase timers (thread 0, constant-rate clock, 10 ns ticks, summed over workgroups):
-    // ticket, wait, attention, output projection + LayerNorm, next layer's Q|K|V, rows out + K|V, publish
+    // ticket, wait, attention, output projection + LayerNorm, next layer's Q|K|V, rows out + K|V, publish; with the
+    // feed-forward sub-block the last one has everything from the output projection to its end, the fourth nothing
     uint64_t prof[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     uint64_t tick = 0;
     if (TIMERS && tid == 0) tick = wall_clock64();

@@ -258,8 +258,8 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
     const int64_t N = p.n_rows;
     uint32_t* flags = p.flags + (int64_t)slice * N;
 
-    // phase timers (DG4_PROFILE): ticket, wait, attention, exchange + output projection + LayerNorm, next
-    // layer's Q|K|V, rows out + K|V, publish, feed-forward
+    // phase timers (DG4_PROFILE): ticket, first projection + wait, attention + exchange, output projection + LayerNorm,
+    // next layer's Q|K|V, rows out + K|V, publish, feed-forward
     uint64_t* ticks = (uint64_t*)(heads_smem + LDS::off_ticks);  // eight sums, the last reading
     auto lap = [&](int which) __attribute__((always_inline)) {
         if (p.prof && tid == 0) {
