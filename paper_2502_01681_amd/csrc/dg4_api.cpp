@@ -27,11 +27,11 @@ int check_cfg(const dg4_layer_cfg* c, bool need_layers)
     return DG4_OK;
 }
 
-// Workspace of dg4_layer_fwd, in bytes from the (256-byte aligned) base. The buffers of the kernel that spreads heads
-// over compute units share the room of buffers that only the other paths use (behind the K | V store; in front of it the
-// feed-forward sweep of a wide circuit was 0.6 % slower, 1701 against 1711 us, by where its rows came to lie); the
-// status words lie behind both. The size covers both, so that it depends on the configuration, the number of gates
-// and the largest level only, not on the path: what is enough for a circuit is enough for a smaller one.
+// Workspace of dg4_layer_fwd, in bytes from the (256-byte aligned) base. Every buffer that some path of the configuration
+// needs is there, so that size and layout depend on the configuration, the number of gates and the largest level only,
+// not on the path: what is enough for a circuit is enough for a smaller one. (The buffers of the kernel that spreads heads
+// over compute units are 28 bytes per gate at most and up to 7.4 MB. Sharing the room of buffers that only the other
+// paths use costs 0.5 to 1.3 % on small circuits or wide ones, by where rows and polled words come to lie.)
 struct LayerPlan {
     size_t wqkv[DG4_MAX_LAYERS], wo[DG4_MAX_LAYERS];
     size_t w1[DG4_MAX_LAYERS], w2[DG4_MAX_LAYERS];   // feed-forward weights, packed (DG4_FFN)
@@ -49,15 +49,14 @@ struct LayerPlan {
     size_t ffn_t;        // persistent sweep: W1 | W2 in its streaming order (DG4_FFN)
     size_t park;         // persistent sweep: rows parked between the two tiles of a pair (DG4_FFN)
     size_t bias_all;     // [n_layers][heads, 4] float: the relation biases of every layer, contiguous
-    size_t flags;        // [n] uint32 "rows published"
-    size_t heads_bias, heads_flags;      // heads spread over compute units: the biases, [heads, n] uint32 "rows published"
-    size_t sync, exchange;       // ... counters and mailboxes, words in flight between the slices
+    size_t flags;        // [n] uint32 "rows published" (heads spread over compute units: [heads, n])
+    size_t sync, exchange;       // heads spread over compute units: counters and mailboxes, words in flight between the slices
     size_t ctrl;         // abort word, ticket counter, phase timers
     size_t total;
     int64_t max_rows;
 };
 
-// Whether there are circuits whose sweeps under this configuration (level by level or not) run that way.
+// Whether there are circuits that heads_route takes under this configuration (DG4_PER_LEVEL left aside).
 bool heads_config(const dg4_layer_cfg* c)
 {
     if (c->flags & DG4_BOUNDED_KV) return false;
@@ -111,7 +110,6 @@ LayerPlan plan_layer(const dg4_layer_cfg* c, const dg4_graph* g)
     // K | V rows: of every finished gate, or (DG4_BOUNDED_KV) of one level's frontier only
     p.kv_rows = bounded ? (size_t)std::max<int64_t>(g->front_max, 1) : n;
     p.kv = take(L * p.kv_rows * 2 * d * es);
-    const size_t shared = off;
     p.hpos = take(bounded ? 0 : n * d * es);
     p.abuf = take((size_t)mr * d * es);
     p.s0 = take((size_t)mr * d * es);
@@ -123,16 +121,10 @@ LayerPlan plan_layer(const dg4_layer_cfg* c, const dg4_graph* g)
     p.ffn_t = take(ffn ? 2 * d * 4 * d * es : 0);
     p.park = take(ffn ? (size_t)DG4_MAX_SWEEP_GROUPS * DG4_TILE_ROWS * d * es : 0);
     p.bias_all = take(L * (size_t)c->heads * 4 * sizeof(float));
-    p.flags = take(n * sizeof(uint32_t));
-    if (heads_config(c)) {
-        const size_t others = off;
-        off = shared;
-        p.heads_bias = take(L * (size_t)c->heads * 4 * sizeof(float));
-        p.heads_flags = take(n * sizeof(uint32_t) * (size_t)c->heads);
-        p.sync = take(DG4_HEADS_SYNC_BYTES);
-        p.exchange = take((size_t)dg4_heads_exchange_bytes(c->dtype, c->hidden, ffn, dg4_head_groups(c->heads)));
-        off = std::max(others, off);
-    }
+    const bool heads = heads_config(c);
+    p.flags = take(n * sizeof(uint32_t) * (heads ? (size_t)c->heads : 1));
+    p.sync = take(heads ? DG4_HEADS_SYNC_BYTES : 0);
+    p.exchange = take(heads ? (size_t)dg4_heads_exchange_bytes(c->dtype, c->hidden, ffn, dg4_head_groups(c->heads)) : 0);
     p.ctrl = take(256);
     p.total = off;
     return p;
@@ -415,8 +407,8 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
             a.ffn = 1; a.w1_packed = at(pl.w1[0]); a.w2_packed = at(pl.w2[0]);
             a.ffn_layer_stride = L > 1 ? (int64_t)(pl.w1[1] - pl.w1[0]) : 0;
         }
-        a.rel_bias = (const float*)at(pl.heads_bias);
-        a.flags = (uint32_t*)at(pl.heads_flags); a.sync = (uint32_t*)at(pl.sync); a.exchange = (uint64_t*)at(pl.exchange);
+        a.rel_bias = (const float*)at(pl.bias_all);
+        a.flags = (uint32_t*)at(pl.flags); a.sync = (uint32_t*)at(pl.sync); a.exchange = (uint64_t*)at(pl.exchange);
         a.ctrl = (uint32_t*)at(pl.ctrl);
         a.n_layers = L; a.ln_eps = cfg->ln_eps; a.epilogue = epi ? 1 : 0;
         a.spin_limit = spin_limit;
@@ -430,7 +422,7 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
             }
             k.wqkv_packed = at(pl.wqkv[0]); k.wo_packed = at(pl.wo[0]); k.w_layer_stride = a.w_layer_stride;
             if (ffn) { k.w1_packed = at(pl.w1[0]); k.w2_packed = at(pl.w2[0]); k.ffn_layer_stride = a.ffn_layer_stride; }
-            k.bias_all = (float*)at(pl.heads_bias);
+            k.bias_all = (float*)at(pl.bias_all);
             HIPCHK(dg4_launch_heads_pack(dt, k, s));
         }
         HIPCHK(bracket([&]() { return dg4_launch_heads(dt, d, a, s); }));
