@@ -78,6 +78,29 @@ template <> struct HeadMma<float> {
     }
 };
 
+template <int N> __device__ __forceinline__ float ror(float x)        // rotated by N inside each row of 16 lanes
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + N, 0xF, 0xF, true));
+}
+// the other quad of each eight lanes
+__device__ __forceinline__ float xor4(float x)
+{
+    const int mirrored = __builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x141, 0xF, 0xF, true);    // lane i of eight: 7 - i
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, mirrored, 0x1B, 0xF, 0xF, true));            // a quad's lanes turned round
+}
+// lane J of each quad
+template <int J> __device__ __forceinline__ float of_quad(float x)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), J * 0x55, 0xF, 0xF, true));
+}
+// d[0..3] summed over the lanes of each quad: lane j of the quad ends with the sum of d[j]
+__device__ __forceinline__ float quad_sums(const float* d, bool odd, bool upper)
+{
+    const float a = (odd ? d[1] : d[0]) + xor1(odd ? d[0] : d[1]);
+    const float b = (odd ? d[3] : d[2]) + xor1(odd ? d[2] : d[3]);
+    return (upper ? b : a) + xor2(upper ? a : b);
+}
+
 // A lane's 16 bytes of a row: 8 bfloat16 or 4 floats
 template <typename T> struct Bits16;
 template <> struct Bits16<float> {
@@ -96,12 +119,9 @@ template <> struct Bits16<float> {
         d = fmaf(__uint_as_float(a.z), __uint_as_float(b.z), d);
         return fmaf(__uint_as_float(a.w), __uint_as_float(b.w), d);
     }
-    // eight lanes hold a head: quads, then the two quads of each eight (the lanes of a quad agree by then)
-    __device__ static __forceinline__ float head_sum(float p)
-    {
-        p += xor1(p); p += xor2(p);
-        return p + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(p), 0x141, 0xF, 0xF, true));
-    }
+    // eight lanes hold a head: the quads q and q + 2 of a row of 16 lanes
+    __device__ static __forceinline__ float head_sum(float p) { p += xor1(p); p += xor2(p); return quads_sum(p); }
+    __device__ static __forceinline__ float quads_sum(float p) { return p + ror<8>(p); }
 };
 template <> struct Bits16<bf16_t> {
     __device__ static __forceinline__ void unpack(const uint4& v, float* f)
@@ -124,7 +144,8 @@ template <> struct Bits16<bf16_t> {
         d0 = d2(a.z, b.z, d0); d1 = d2(a.w, b.w, d1);
         return d0 + d1;
     }
-    __device__ static __forceinline__ float head_sum(float p) { p += xor1(p); p += xor2(p); return p; }    // four lanes hold a head
+    __device__ static __forceinline__ float head_sum(float p) { p += xor1(p); p += xor2(p); return p; }    // a quad holds a head
+    __device__ static __forceinline__ float quads_sum(float p) { return p; }
 };
 
 // lanes 16 apart / 32 apart added or compared, the result in both
@@ -151,10 +172,6 @@ __device__ __forceinline__ float max32(float x)
     const uint32_t u = __float_as_uint(x);
     const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
     return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-}
-template <int N> __device__ __forceinline__ float ror(float x)        // rotated by N inside each row of 16 lanes
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + N, 0xF, 0xF, true));
 }
 
 // 16 bytes written through to device memory (agent scope); not tracked by the compiler's wait counting: the
@@ -198,15 +215,21 @@ template <typename T, int D, int W> struct HeadsLds {            // byte offsets
     static constexpr size_t CTL = 64 + DG4_MAX_LAYERS * 4 * sizeof(float);
     static constexpr size_t off_qkv = 2 * ROWS, off_stat = off_qkv + QKV, off_att = off_stat + STAT, off_ctl = off_att + ATT,
                             off_ticks = off_ctl + CTL, off_ent = off_ticks + 80;
+    // words of a neighbour row (W == 0): whole rounds, in which every lane group of the gate takes eight entries
+    __host__ __device__ static constexpr int round_words(int tile_rows) { return 8 * (HT / tile_rows) / (32 * (int)sizeof(T) / 16); }
+    __host__ __device__ static constexpr int row_words(int ell_w, int tile_rows)
+    {
+        return (ell_w + round_words(tile_rows) - 1) / round_words(tile_rows) * round_words(tile_rows);
+    }
     static size_t bytes(int ell_w, int tile_rows, bool ffn)
     {
-        return off_ent + (size_t)tile_rows * ell_w * sizeof(uint32_t) +
+        return off_ent + (size_t)tile_rows * (ell_w > 16 ? row_words(ell_w, tile_rows) : ell_w) * sizeof(uint32_t) +
                (ffn ? (size_t)HR * US * sizeof(T) + (size_t)8 * HR * 32 * sizeof(float) : 0);
     }
 };
 
-// W: entries of a neighbour row (8 or 16; 0: any multiple of four, p.ell_w)
-template <typename T, int D, int W, bool FFN>
+// W: entries of a neighbour row (8 or 16; 0: any multiple of four, p.ell_w). ONE: one layer
+template <typename T, int D, int W, bool FFN, bool ONE>
 __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
 {
     typedef HeadsLds<T, D, W> LDS;
@@ -234,9 +257,10 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
     float* att = (float*)(heads_smem + LDS::off_att);            // [part][32] weighted sums, then [part][2] maximum, denominator
     int* ctl = (int*)(heads_smem + LDS::off_ctl); // this tile's and the next one's {first position, rows}, [8] abort word, [12], [13] place in a group
     float* biases = (float*)(ctl + 16);           // [layers][4] of this head
+    // neighbour rows: what is no source (padding, the gate itself) holds relation 0 and the row past the store's end
     uint32_t* ent = (uint32_t*)(heads_smem + LDS::off_ent);
-    const int ell_w = W ? W : p.ell_w;
     const int tile_rows = W ? HR : p.tile_rows;
+    const int ell_w = W ? W : LDS::row_words(p.ell_w, tile_rows);
     T* ubuf = (T*)(heads_smem + LDS::off_ent + (size_t)tile_rows * ell_w * sizeof(uint32_t));      // (FFN) the 4D activations
     float* red = (float*)((unsigned char*)ubuf + (size_t)HR * LDS::US * sizeof(T));                // (FFN) [8][16][32] partial sums
 
@@ -254,7 +278,7 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
     // (what derives from the slice likewise: it is a value like any other once the workgroup has its seat, and kept across
     // the loops its products cost up to 15 scalar registers more in spills, 0.9 % of a two-layer sweep at bf16 / 128)
     auto next_phase = [&]() __attribute__((always_inline)) { phase(tid); __asm__ volatile("" : "+s"(slice)); };
-    const int L = p.n_layers;
+    const int L = ONE ? 1 : p.n_layers;
     const int64_t N = p.n_rows;
     uint32_t* flags = p.flags + (int64_t)slice * N;
 
@@ -536,13 +560,29 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
             const int64_t id = p.order[p0 + row];
             *(uint4*)&resid[row * YS + c * E] = *((const uint4*)((const T*)p.x + id * D) + c);
         }
-        for (int i = tid; i < rows * (ell_w / 4); i += HT)
-            ((uint4*)ent)[i] = ((const uint4*)(p.ell + p0 * (int64_t)ell_w))[i];
+        const auto no_source = [&](uint32_t e) __attribute__((always_inline)) { return e == DG4_ELL_PAD || (e >> 30) == 0 ? (uint32_t)N : e; };
+        auto put4 = [&](int i, const uint4& e) __attribute__((always_inline)) {
+            ((uint4*)ent)[i] = make_uint4(no_source(e.x), no_source(e.y), no_source(e.z), no_source(e.w));
+        };
+        if constexpr (W != 0) {
+            for (int i = tid; i < rows * (W / 4); i += HT) put4(i, ((const uint4*)(p.ell + p0 * (int64_t)W))[i]);
+        } else {
+            // entry i of a round lies where lane group i % SG finds its (i / SG)-th: a group reads its eight entries as two
+            // 16-byte words, and the groups of a row request ask for entries side by side
+            const int row = tid >> p.lanes_log2, lanes = HT / tile_rows, sg_log2 = p.lanes_log2 - (LPS == 4 ? 2 : 3);
+            for (int c = tid & (lanes - 1); c < ell_w / 4; c += lanes) {
+                uint4 e = make_uint4(DG4_ELL_PAD, DG4_ELL_PAD, DG4_ELL_PAD, DG4_ELL_PAD);
+                if (row < rows && 4 * c < p.ell_w) e = *(const uint4*)(p.ell + (p0 + row) * p.ell_w + 4 * c);
+                const int i = (4 * c) & ((8 << sg_log2) - 1);
+                uint32_t* to = ent + row * ell_w + (4 * c - i) + (i & ((1 << sg_log2) - 1)) * 8 + (i >> sg_log2);
+                to[0] = no_source(e.x); to[8] = no_source(e.y); to[16] = no_source(e.z); to[24] = no_source(e.w);
+            }
+        }
         heads_barrier();
 
         uint4 b[S];
         f32x4 acc[UT];
-        // this head's Q | K | V of the running state; then the output projection's weights are requested
+        // this head's Q | K | V of the running state
         auto project = [&](const T* rows_of, int l) __attribute__((always_inline)) {
             if (qkv_wave) {
                 load_rows(rows_of, b);
@@ -551,38 +591,54 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
                 cols_of(acc, v);
                 *(uint4*)&qkv[n * QS + (wave / UH) * 32 + (wave % UH) * UC + g * CW] = Bits16<T>::pack(v);
             }
-            if (W || L > 1) fill_wo(l);
         };
-        // Attention roles: SG lane groups of LPS lanes share a gate, group i takes the entries i, i + SG, ..., CH at
-        // a time. The K | V of a group's first CH entries are requested a layer ahead (the sources are finished in
-        // every layer), so that from the second layer on a narrow row waits for no memory.
+        // Attention roles: SG lane groups of LPS lanes share a gate (a group is a quad of lanes in bfloat16, the quads q
+        // and q + 2 of 16 lanes in fp32). Rows of 8 and 16 entries: group i takes the entries i, i + SG, ...; the K | V
+        // are requested a layer ahead (the sources are finished in every layer), so that from the second layer on
+        // a narrow row waits for no memory. Wider rows: rounds of eight entries per group, dealt likewise.
         constexpr int SGN = HT / HR / LPS;        // (rows of 8 or 16 entries: tiles of 16)
         constexpr int CH = W ? W / SGN : 8;
         uint4 k4[CH], v4[CH];
         uint32_t en[CH];
         const int lpg = HT / tile_rows, SG = lpg / LPS;           // lanes of a gate: 32 (16 gates) to 256 (2 gates)
         auto gate_of = [&]() __attribute__((always_inline)) { return W ? tid / (HT / HR) : tid >> p.lanes_log2; };
-        auto group_of = [&]() __attribute__((always_inline)) { return (tid & (lpg - 1)) / LPS; };
-        auto entries = [&](int c0) __attribute__((always_inline)) {
-            const int r = gate_of();
-#pragma unroll
-            for (int j = 0; j < CH; ++j) en[j] = r < rows && (W || c0 + SG * j < ell_w) ? ent[r * ell_w + c0 + SG * j] : DG4_ELL_PAD;
+        auto group_of = [&]() __attribute__((always_inline)) {
+            const int t = tid & (lpg - 1);
+            return LPS == 4 ? t >> 2 : (t >> 4) * 2 + ((t >> 2) & 1);
         };
-        auto is_source = [&](uint32_t e) __attribute__((always_inline)) { return e != DG4_ELL_PAD && (e >> 30) != 0; };
-        // (K and V of an entry back to back: they share a cache line)
+        auto sub_of = [&]() __attribute__((always_inline)) { return LPS == 4 ? tid & 3 : (tid & 3) | ((tid >> 1) & 4); };
+        auto piece = [&](const uint32_t* at) __attribute__((always_inline)) {
+            const uint4 a = ((const uint4*)at)[0], b = ((const uint4*)at)[1];
+            en[0] = a.x; en[1] = a.y; en[2] = a.z; en[3] = a.w;
+            en[CH - 4] = b.x; en[CH - 3] = b.y; en[CH - 2] = b.z; en[CH - 1] = b.w;
+        };
+        auto rows_of_layer = [&](int l) __attribute__((always_inline)) {
+            return row_buffer((const T*)p.kv + ((int64_t)l * C + slice) * N * 64, 64 * sizeof(T), (uint32_t)N);
+        };
+        // (an entry that is no source asks for the row past the end: zeros, no request. K and V of an entry back to back: they
+        // share a cache line, which is gone from the L1 when all K rows of a round are asked for first.)
         auto request = [&](int l) __attribute__((always_inline)) {
-            const dg4_i32x4 kvb = row_buffer((const T*)p.kv + ((int64_t)l * C + slice) * N * 64, 64 * sizeof(T), (uint32_t)N);
-            const uint32_t off = (uint32_t)(tid % LPS) * 16u;
+            const dg4_i32x4 kvb = rows_of_layer(l);
+            const uint32_t off = (uint32_t)sub_of() * 16u;
 #pragma unroll
-            for (int j = 0; j < CH; ++j) {        // (an entry that is no source asks for the row past the end: zeros, no request)
-                const uint32_t row = is_source(en[j]) ? (en[j] & 0x3FFFFFFFu) : (uint32_t)N;
-                k4[j] = row_load16(kvb, row, off);
-                v4[j] = row_load16(kvb, row, (uint32_t)(32 * sizeof(T)) + off);
+            for (int j = 0; j < CH; ++j) {
+                k4[j] = row_load16(kvb, en[j] & 0x3FFFFFFFu, off);
+                v4[j] = row_load16(kvb, en[j] & 0x3FFFFFFFu, off + (uint32_t)(32 * sizeof(T)));
+                __builtin_amdgcn_sched_barrier(0);
             }
+        };
+        auto is_source = [&](uint32_t e) __attribute__((always_inline)) { return (e >> 30) != 0; };
+        // (W != 0) the sources of a layer
+        auto request_first = [&](int l) __attribute__((always_inline)) {
+            const int r = gate_of(), grp = group_of();
+#pragma unroll
+            for (int j = 0; j < CH; ++j) en[j] = r < rows ? ent[r * W + grp + SG * j] : (uint32_t)N;
+            request(l);
         };
         {
             next_phase();
             project(resid, 0);
+            if (W || !ONE) fill_wo(0);
             next_phase();
             // ---- the sources of the tile's gates must be published (in this slice)
             {
@@ -598,10 +654,9 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
 #pragma unroll
                         for (int q = 0; q < Q; ++q) {
                             const int i = next + HT * q;
-                            const uint32_t e = i < count ? ent[i] : DG4_ELL_PAD;
-                            const bool watch = e != DG4_ELL_PAD && (e >> 30) != 0;
+                            const uint32_t e = i < count ? ent[i] : 0u;
                             seen[q] = 1u;
-                            if (watch) seen[q] = __hip_atomic_load(flags + (e & 0x3FFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            if (e >> 30) seen[q] = __hip_atomic_load(flags + (e & 0x3FFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         }
 #pragma unroll
                         for (int q = 0; q < Q; ++q) ok = ok && seen[q] != 0u;
@@ -616,14 +671,14 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
             }
             heads_barrier();
             lap(1);
-            if (W) { entries(group_of()); request(0); }
+            if (W) request_first(0);
 #pragma unroll 1
             for (int l = 0; l < L; ++l) {
-                const bool last = l == L - 1;
+                const bool last = ONE || l == L - 1;
                 // ---- attention with this head: a running maximum, denominator and weighted sum per lane group
                 {
                     next_phase();
-                    const int r = gate_of(), grp = group_of(), sub = tid % LPS;
+                    const int r = gate_of(), grp = group_of(), sub = sub_of();
                     const float* bp = biases + 4 * l;
                     const float bias[4] = { bp[0], bp[1], bp[2], bp[3] };
                     const float scale = 0.17677669529663687f;     // 1/sqrt(32)
@@ -639,12 +694,7 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
 #pragma unroll
                         for (int i = 0; i < E; ++i) av[i] = own ? z * v[i] : 0.f;
                     }
-                    for (int c0 = grp; c0 < ell_w; c0 += SG * CH) {
-                        if constexpr (W == 0) {
-                            entries(c0);
-                            if (en[0] == DG4_ELL_PAD) break;      // rows are padded at the end only
-                            request(l);
-                        }
+                    if constexpr (W != 0) {
                         float sc[CH], cm = m;
 #pragma unroll
                         for (int j = 0; j < CH; ++j) {
@@ -668,18 +718,70 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
                             for (int i = 0; i < E; ++i) av[i] = fmaf(pj, v[i], av[i]);
                         }
                         m = cm;
+                    } else {
+                        // Eight entries a lane group and round: lane j of a quad ends with the scores of the entries j and j + 4, so
+                        // that a score is scaled, masked and exponentiated once and not by every lane of the head, and hands its
+                        // weights to the quad: 180 vector instructions a round in fp32, where every lane of a head computing every
+                        // score behind a bounds check per entry took 400. Rows of 240 entries: 7.74 -> 7.27 ms with twelve layers at
+                        // 15,135 gates in fp32 / 128, 14.1 -> 12.8 at 39,001 with feed-forward in bf16 / 128, 12.5 -> 11.6 with one
+                        // layer at 201,024 in bf16 / 256. What is left is the way from the L2 to the registers: 245 KB per compute
+                        // unit, layer and tile, 2 us at the 124 GB/s a unit reaches from its L2 with nothing else to do, about 3.5
+                        // here. Measured and not kept: the next round's K | V requested under this round's arithmetic (the requests
+                        // behind the last round cost what it gains), the first round of the next layer requested during the LayerNorm
+                        // (its waves then wait to issue), the next layer's rows touched once per L2.
+                        const bool odd = (sub & 1) != 0, upper = (sub & 2) != 0;
+                        float zq = 0.f;           // this lane's entries of z
+                        const uint32_t* at = ent + r * ell_w + grp * CH;
+                        for (int c0 = 0; c0 < ell_w; c0 += SG * CH, at += SG * CH) {
+                            piece(at);
+                            // rows are padded at the end only: where none of the wave's groups has a source, none follows
+                            uint32_t any = 0;
+#pragma unroll
+                            for (int j = 0; j < CH; ++j) any |= en[j];
+                            if (__ballot(any >> 30 != 0) == 0) break;
+                            request(l);
+                            const uint32_t e0 = at[sub & 3], e1 = at[4 + (sub & 3)];
+                            float d[CH];
+#pragma unroll
+                            for (int j = 0; j < CH; ++j) d[j] = Bits16<T>::dot(q4, k4[j]);
+                            const float bb0 = e0 >> 30 == 1 ? bias[1] : e0 >> 30 == 2 ? bias[2] : bias[3];
+                            const float bb1 = e1 >> 30 == 1 ? bias[1] : e1 >> 30 == 2 ? bias[2] : bias[3];
+                            const float d0 = fmaf(Bits16<T>::quads_sum(quad_sums(d, odd, upper)), scale, bb0);
+                            const float d1 = fmaf(Bits16<T>::quads_sum(quad_sums(d + CH - 4, odd, upper)), scale, bb1);
+                            const float s0 = is_source(e0) ? d0 : -INFINITY, s1 = is_source(e1) ? d1 : -INFINITY;
+                            float cm = fmaxf(s0, s1);
+                            cm = fmaxf(cm, xor1(cm));
+                            cm = fmaxf(m, fmaxf(cm, xor2(cm)));
+                            const float corr = __expf(m - cm), p0 = __expf(s0 - cm), p1 = __expf(s1 - cm);
+                            m = cm;
+                            z *= corr;
+                            zq = fmaf(zq, corr, p0 + p1);
+#pragma unroll
+                            for (int i = 0; i < E; ++i) av[i] *= corr;
+                            const float pj[8] = { of_quad<0>(p0), of_quad<1>(p0), of_quad<2>(p0), of_quad<3>(p0),
+                                                  of_quad<0>(p1), of_quad<1>(p1), of_quad<2>(p1), of_quad<3>(p1) };
+#pragma unroll
+                            for (int j = 0; j < CH; ++j) {
+                                float v[E];
+                                Bits16<T>::unpack(v4[j], v);
+#pragma unroll
+                                for (int i = 0; i < E; ++i) av[i] = fmaf(pj[j], v[i], av[i]);
+                            }
+                        }
+                        zq += xor1(zq);
+                        z += zq + xor2(zq);
                     }
                     // the groups of a wave that share a gate, merged (all lanes take part)
                     float mm = m;
                     if (LPS == 4) mm = fmaxf(mm, ror<4>(mm));
-                    mm = fmaxf(mm, ror<8>(mm));
+                    mm = fmaxf(mm, LPS == 4 ? ror<8>(mm) : xor4(mm));
                     mm = max16(mm);
                     if (tile_rows <= 8) mm = max32(mm);
                     const float f = __expf(m - mm);
                     auto total_of = [&](float x) __attribute__((always_inline)) {
                         x *= f;
                         if (LPS == 4) x += ror<4>(x);
-                        x += ror<8>(x);
+                        x += LPS == 4 ? ror<8>(x) : xor4(x);
                         x = add16(x);
                         return tile_rows <= 8 ? add32(x) : x;
                     };
@@ -687,7 +789,7 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
 #pragma unroll
                     for (int i = 0; i < E; ++i) av[i] = total_of(av[i]);
                     const int part = tile_rows == 16 ? r : tid >> 6;      // waves of a gate are consecutive
-                    if ((tid & (tile_rows == 16 ? 31 : 63)) < LPS) {
+                    if (grp % (tile_rows == 16 ? 32 / LPS : 64 / LPS) == 0) {
                         *(float4*)&att[part * 32 + sub * E] = make_float4(av[0], av[1], av[2], av[3]);
                         if (E == 8) *(float4*)&att[part * 32 + sub * E + 4] = make_float4(av[E - 4], av[E - 3], av[E - 2], av[E - 1]);
                         if (sub == 0) { att[HR * 32 + 2 * part] = mm; att[HR * 32 + 2 * part + 1] = z; }
@@ -715,7 +817,7 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
                     put_word(xa + (int64_t)r * WPR + slice * WPS + w,
                              sizeof(T) == 4 ? __float_as_uint(v0 * rz) : pack_bf16x2(v0 * rz, v1 * rz), tag);
                 }
-                if (!W && L == 1) fill_wo(0);     // (not before the gathers)
+                if (!W && ONE) fill_wo(0);        // (not before the gathers)
                 // ---- ... and theirs come in
                 collect(xa, rows * WPR, tag, std::integral_constant<int, HR * WPR / HT>{}, [&](int i, uint32_t data) __attribute__((always_inline)) {
                     *(uint32_t*)((unsigned char*)(ybuf + (i / WPR) * YS) + (i % WPR) * 4) = data;
@@ -738,10 +840,7 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
                 if (FFN) fill_w1(l);
                 else if (!last) fill_qkv(l + 1);
                 else fill_kv(wave);
-                if (W && !last) {                 // the next layer's sources
-                    entries(group_of());
-                    request(l + 1);
-                }
+                if (W && !ONE && !last) request_first(l + 1);       // the next layer's sources
                 next_phase();
                 if (p.epilogue) {
                     if (wo_wave) {
@@ -891,6 +990,7 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
                     next_phase();
                     // ---- this head's Q | K | V of the new state
                     project(ybuf, l + 1);
+                    fill_wo(l + 1);
                     T* tmp = resid; resid = ybuf; ybuf = tmp;     // the new state is the next layer's residual
                     heads_barrier();
                     lap(4);
@@ -976,9 +1076,14 @@ int launch_heads_t(const dg4_heads_args& a, int64_t groups, hipStream_t s)
     if (!wide && a.tile_rows != HR) return hipErrorInvalidValue;
     if (a.n_pre * HR < a.pre_rows || (a.ffn && (!a.w1_packed || !a.w2_packed))) return hipErrorInvalidValue;
     void (*kern)(dg4_heads_args) = nullptr;
-    if (a.ell_w == 8) kern = a.ffn ? heads_kernel<T, D, 8, true> : heads_kernel<T, D, 8, false>;
-    else if (a.ell_w == 16) kern = a.ffn ? heads_kernel<T, D, 16, true> : heads_kernel<T, D, 16, false>;
-    else kern = a.ffn ? heads_kernel<T, D, 0, true> : heads_kernel<T, D, 0, false>;
+    const auto pick = [&](auto w) -> void (*)(dg4_heads_args) {
+        constexpr int W = decltype(w)::value;
+        if (a.ffn) return heads_kernel<T, D, W, true, false>;
+        return a.n_layers == 1 ? heads_kernel<T, D, W, false, true> : heads_kernel<T, D, W, false, false>;
+    };
+    if (a.ell_w == 8) kern = pick(std::integral_constant<int, 8>{});
+    else if (a.ell_w == 16) kern = pick(std::integral_constant<int, 16>{});
+    else kern = pick(std::integral_constant<int, 0>{});
     const size_t smem = HeadsLds<T, D, 0>::bytes(a.ell_w, a.tile_rows, a.ffn != 0);
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;

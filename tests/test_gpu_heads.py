@@ -331,3 +331,27 @@ def test_heads_kernel_takes_two_tiles_of_the_pair_table_at_a_time(hidden, dtype,
     assert torch.equal(H, run(w, cfg, deeper, fw))
     edges = [torch.from_numpy(a).cuda() for a in (w.edge_src, w.edge_dst, w.edge_inv, hint)]
     assert torch.equal(H, run(w, cfg, dg4.dg4_build_levels_device(c.n_nodes, *edges[:3], hops, edges[3]), fw))
+
+
+@pytest.mark.parametrize("hidden,dtype,layers", [(128, "f32", 1), (128, "bf16", 2), (256, "f32", 2), (256, "bf16", 1)])
+@pytest.mark.parametrize("hops,trees", [(4, 3), (5, 3), (6, 20), (7, 20), (8, 3)])
+def test_heads_kernel_on_rows_that_end_a_round(hidden, dtype, layers, hops, trees):
+    # complete trees: rows of 2^(h+1) - 1 entries, so that whole rounds of a lane group's eight entries, one entry
+    # short (the gate itself included), come in every tile size and lane split
+    leaves = 2 ** hops
+    n_pi, n_and = trees * leaves, trees * (leaves - 1)
+    w = make(n_and, 2, hidden, dtype, hops, layers, n_pi=n_pi)
+    src, dst, below, nxt = [], [], np.arange(n_pi), n_pi
+    while len(below) > trees:
+        above = np.arange(nxt, nxt + len(below) // 2)
+        src.append(below)
+        dst.append(np.repeat(above, 2))
+        below, nxt = above, nxt + len(above)
+    src, dst = np.concatenate(src).astype(np.int32), np.concatenate(dst).astype(np.int32)
+    inv = (np.arange(len(src)) % 3 == 0).astype(np.uint8)
+    g = dg4.dg4_build_levels(w.cfg.n_nodes, src, dst, inv, hops)
+    assert max(np.diff(g.array("nbr_ptr"))) == 2 ** (hops + 1) - 1
+    print(f"tree rows {dtype} {hidden} hops={hops} trees={trees} layers={layers}", flush=True)
+    H = run(w, cfg_of(w.cfg), g)
+    og = oracle.build_levels(w.cfg.n_nodes, src, dst, inv, hops)
+    assert row_rel_err(to_np(H), oracle.layer_fwd(og, w.x, w.wqkv, w.wo, w.rel_bias, w.cfg.heads, store=dtype)).max() <= TOL[dtype]
