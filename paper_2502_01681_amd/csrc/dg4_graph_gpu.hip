@@ -546,6 +546,32 @@ __global__ void position_kernel(int64_t n, const int32_t* order, int32_t* pos)
     if (r < n) pos[order[r]] = (int32_t)r;
 }
 
+// The processing order inside the levels, for whole cone rows (dg4_graph_ensure_device has its rule): gates that some gate at
+// most two levels up reads first, each part by the position of the latest fanin.
+__global__ void read_soon_kernel(int64_t n, const int32_t* fin, const int32_t* deg, const int32_t* level, uint8_t* soon)
+{
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= n) return;
+    for (int k = 0; k < deg[v]; ++k) {
+        const int32_t u = fin[2 * v + k];
+        if (level[v] - level[u] <= 2) soon[u] = 1;            // (every writer writes the same)
+    }
+}
+__global__ void latest_fanin_kernel(int64_t n, const int32_t* order, const int32_t* fin, const int32_t* deg, const int32_t* pos, uint32_t* key)
+{
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= n) return;
+    const int64_t v = order[r];
+    int32_t latest = -1;
+    for (int k = 0; k < deg[v]; ++k) latest = max(latest, pos[fin[2 * v + k]]);
+    key[r] = (uint32_t)(latest + 1);
+}
+__global__ void level_part_kernel(int64_t n, const int32_t* order, const int32_t* level, const uint8_t* soon, uint32_t* key)
+{
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r < n) key[r] = 2u * (uint32_t)level[order[r]] + (soon[order[r]] ? 0u : 1u);      // (below 2^31: n < 2^30 - 1)
+}
+
 // Packed neighbour rows of nodes v0 .. v0 + count - 1 in a fixed-width table: a node's row at its position (pos null:
 // at its id), entries by position (by id) in ascending-id order, padded. ptr, idx, rel: these nodes' part of the CSR;
 // first: the entry idx begins with; pad: empty rows behind position v0 + count. Four entries per thread; bound by the
@@ -701,6 +727,31 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
             if (ptr_prev != nbr_ptr)             // the last hop's pointers, where the copies below expect them
                 GPU_CHECK(hipMemcpyAsync(nbr_ptr, ptr_prev, ((size_t)n + 1) * sizeof(int64_t), hipMemcpyDeviceToDevice, s));
         }
+        // Processing order: where the host walks the levels one after the other (2.1 ms for 102 K gates), two stable sorts over all
+        // gates, by the latest fanin's position and then by (level, read late), from (level, id) positions first and from
+        // those of the first result after that: it tells apart what the first result already has in its place, which
+        // is the part of the order that a sweep's time depends on.
+        int32_t* sweep = nullptr;
+        int32_t* pos = nullptr;
+        if (stride == 0) {
+            GPU_ALLOC(soon, uint8_t, (size_t)n, true);
+            GPU_ALLOC(key, uint32_t, (size_t)n, false);
+            sweep = arena.get<int32_t>((size_t)n, false, s);
+            pos = arena.get<int32_t>((size_t)n, false, s);
+            if (!sweep || !pos) return DG4_ENOMEM;
+            int pos_bits = 1, part_bits = 1;
+            while ((n >> pos_bits) != 0) ++pos_bits;          // keys 0 .. n
+            while (((2 * (int64_t)h_max + 1) >> part_bits) != 0) ++part_bits;
+            hipLaunchKernelGGL(read_soon_kernel, dim3(nb), dim3(256), 0, s, n, fin, deg, level, soon);
+            hipLaunchKernelGGL(position_kernel, dim3(nb), dim3(256), 0, s, n, (const int32_t*)order, pos);
+            for (int look = 0; look < 2; ++look) {
+                hipLaunchKernelGGL(latest_fanin_kernel, dim3(nb), dim3(256), 0, s, n, order, fin, deg, pos, key);
+                sort_pairs(key, order, (uint32_t*)sorted_level, ids, n, pos_bits, sort_keys, sort_vals, sort_hist, scan_sums, s);
+                hipLaunchKernelGGL(level_part_kernel, dim3(nb), dim3(256), 0, s, n, (const int32_t*)ids, level, soon, key);
+                sort_pairs(key, ids, (uint32_t*)sorted_level, sweep, n, part_bits, sort_keys, sort_vals, sort_hist, scan_sums, s);
+                hipLaunchKernelGGL(position_kernel, dim3(nb), dim3(256), 0, s, n, (const int32_t*)sweep, pos);
+            }
+        }
         // ---- partition and updating strategy: roots, mini-batch numbers, rows restricted to the cones
         // a gate shares with the mini-batch that computes it (the host analysis, step by step)
         int32_t* stage = nullptr;
@@ -800,8 +851,14 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
             g->stage.resize((size_t)n);
             GPU_CHECK(hipMemcpyAsync(g->stage.data(), stage, (size_t)n * 4, hipMemcpyDeviceToHost, s));
         }
+        if (sweep) {
+            g->sweep_order.resize((size_t)n);
+            GPU_CHECK(hipMemcpyAsync(g->sweep_order.data(), sweep, (size_t)n * 4, hipMemcpyDeviceToHost, s));
+            GPU_CHECK(hipMemcpyAsync(g->pos.data(), pos, (size_t)n * 4, hipMemcpyDeviceToHost, s));
+        }
         GPU_CHECK(hipStreamSynchronize(s));
-        for (int64_t p = 0; p < n; ++p) g->pos[(size_t)g->order[(size_t)p]] = (int32_t)p;
+        if (!sweep)
+            for (int64_t p = 0; p < n; ++p) g->pos[(size_t)g->order[(size_t)p]] = (int32_t)p;
         *out = g.release();
         return DG4_OK;
     } catch (const std::bad_alloc&) {

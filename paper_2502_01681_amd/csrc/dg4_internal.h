@@ -31,7 +31,7 @@ struct dg4_graph {
     int32_t hops = 0, max_level = 0;
     std::vector<int32_t> level, order;           // order: ids by (level, id)
     std::vector<int32_t> pos;                    // pos[id] = position in the level-ordered device processing order (set at upload)
-    std::vector<int32_t> sweep_order;            // its inverse: position -> id
+    std::vector<int32_t> sweep_order;            // its inverse: position -> id (whole cone rows analysed on the GPU: both set at build time)
     std::vector<int64_t> level_ptr, nbr_ptr;
     std::vector<int32_t> out_and, out_not;       // fanout counts of the structural encoding (Eq. 2)
     int32_t* d_struct = nullptr;                 // device [n][3]: level, OutAND, OutNOT (on first dg4_struct_encode)
