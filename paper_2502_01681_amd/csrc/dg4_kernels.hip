@@ -373,13 +373,17 @@ __global__ __launch_bounds__(256) void gemm_kernel(dg4_gemm_args p)
 // AW > 0: the rows' operand is not read from memory but computed here, the attention of the 32
 // rows over neighbour rows of width AW (attend_row, two or four rows per lane group, through LDS
 // into the operand layout): attention, output projection, LayerNorm and K | V in one launch.
+// fp32 / 256 is the largest: as one loop over its 64 fragments the product was not unrolled and read the rows' operand from
+// scratch memory (528 bytes a lane), and with 16 fragments ahead only one workgroup fitted a compute unit. As two loops,
+// with eight (a fragment feeds four products of 64 cycles, so eight are requested 0.9 us ahead), it takes 252 registers and
+// two workgroups overlap: a sweep level by level over 301,024 gates 5.37 -> 3.80 ms, two layers over 101,024 4.88 -> 3.50.
 template <typename T, int D, bool KV, int AW>
-__global__ __launch_bounds__(256) void gemm_ln_split_kernel(dg4_gemm_args p, dg4_attn_args t)
+__global__ __launch_bounds__(256, sizeof(T) == 4 && D == 256 ? 2 : 1) void gemm_ln_split_kernel(dg4_gemm_args p, dg4_attn_args t)
 {
     constexpr int E = 16 / sizeof(T);
     constexpr int KC = D / (2 * E);
     constexpr int NTW = D / 32 / 4;               // column tiles per wave
-    constexpr int RING = 16;
+    constexpr int RING = sizeof(T) == 4 && D == 256 ? 8 : 16;
     constexpr int GROUP = KC > RING ? KC : RING;
     static_assert((NTW * KC) % GROUP == 0, "whole groups per wave");
     __shared__ float part[2][4][32];
@@ -445,14 +449,15 @@ __global__ __launch_bounds__(256) void gemm_ln_split_kernel(dg4_gemm_args p, dg4
     }
     f32x16 acc[NTW];
 #pragma unroll
-    for (int j = 0; j < NTW * KC; ++j) {
-        const int c = j % KC, nt = j / KC;
-        if (c == 0) {
+    for (int nt = 0; nt < NTW; ++nt) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[nt][i] = 0.f;
+        for (int i = 0; i < 16; ++i) acc[nt][i] = 0.f;
+#pragma unroll
+        for (int c = 0; c < KC; ++c) {
+            const int j = nt * KC + c;
+            Mma<T>::run(a[c], ring[j % RING], acc[nt]);
+            if (j + RING < NTW * KC) ring[j % RING] = wp[(j + RING) * 64];
         }
-        Mma<T>::run(a[c], ring[j % RING], acc[nt]);
-        if (j + RING < NTW * KC) ring[j % RING] = wp[(j + RING) * 64];
     }
     constexpr int NTW2 = 2 * D / 32 / 4;          // column tiles of K | V per wave
     const uint4* wp2 = (const uint4*)p.kv_w_packed + (int64_t)wave * NTW2 * KC * 64 + lane;
