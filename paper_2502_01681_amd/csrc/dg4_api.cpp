@@ -256,7 +256,7 @@ extern "C" int dg4_ffn_fwd(const dg4_layer_cfg* cfg, const void* S, int64_t row_
     HIPCHK(dg4_launch_pack_ffn_bulk(cfg->dtype, d, W1, W2, workspace, s));
     dg4_ffn_args f{};
     f.h = S; f.h_stride = d;
-    f.w1_packed = workspace;
+    f.w_packed = workspace;
     f.out = Out; f.out_stride = d;
     f.row_begin = row_begin; f.row_end = row_end;
     f.ln_eps = cfg->ln_eps;
@@ -450,10 +450,8 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
             // K | V columns of layer l go to column tiles [l*2d/32, (l+1)*2d/32) of wkv_all
             if ((!resident && !flow) || (resident && level_begin > 0))
                 HIPCHK(dg4_launch_pack_w(dt, W[WS * l], 3 * d, d, 2 * d, d, ws + pl.wkv_all + (size_t)l * 2 * d * d * es, s));
-            if (ffn && !resident && !flow) {
-                HIPCHK(dg4_launch_pack_w(dt, W[WS * l + 3], 4 * d, 0, 4 * d, d, at(pl.w1[l]), s));
-                HIPCHK(dg4_launch_pack_w2(dt, W[WS * l + 4], d, at(pl.w2[l]), s));
-            }
+            // (one stream over w1 and w2, which lie side by side)
+            if (ffn && !resident && !flow) HIPCHK(dg4_launch_pack_ffn_bulk(dt, d, W[WS * l + 3], W[WS * l + 4], at(pl.w1[l]), s));
         }
     }
     auto kv_project = [&](const void* rows, int64_t stride, const int32_t* gather, int64_t r0, int64_t r1) -> int {
@@ -711,7 +709,7 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
             if (ffn) {
                 dg4_ffn_args f{};
                 f.h = local(pl.h1, p0, d); f.h_stride = d;
-                f.w1_packed = at(pl.w1[l]); f.w2_packed = at(pl.w2[l]);
+                f.w_packed = at(pl.w1[l]);
                 f.row_begin = p0; f.row_end = p1; f.ln_eps = cfg->ln_eps;
                 if (last) {
                     f.out = Hout; f.out_stride = d; f.out_scatter = d_order;
@@ -719,7 +717,7 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
                 } else {
                     f.out = next; f.out_stride = d;
                 }
-                HIPCHK(dg4_launch_ffn(dt, d, f, s));
+                HIPCHK(dg4_launch_ffn_bulk(dt, d, f, s));
             }
 
             if (!last) {
