@@ -627,7 +627,7 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
     const int32_t lev_end = compact ? (int32_t)lptr.size() - 1 : level_end;
     const int32_t lev_count = compact ? (int32_t)lptr.size() - 1 : n_levels;
     // one layer without feed-forward sub-block: the output projection's launch also projects K | V
-    const bool fuse_kv = L == 1 && !ffn && !bounded && epi && dg4_gemm_fuses_kv(dt, d);
+    const bool fuse_kv = L == 1 && !ffn && !bounded && epi;
 
     // layer 0 projections of x for every gate of the swept levels, in one pass (level by level
     // further down if nothing of the size of the graph may be kept)
@@ -680,7 +680,7 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
             // narrow rows, a level of few gates (bound by the latency of its launches): the attention
             // runs inside the output projection's launch. The same arithmetic either way, so the
             // choice by the size of the level does not show in the result.
-            const bool fuse_att = epi && g->ell_w <= 16 && p1 - p0 <= 4096 && dg4_gemm_fuses_kv(dt, d);
+            const bool fuse_att = epi && g->ell_w <= 16 && p1 - p0 <= 4096;
             if (!fuse_att) HIPCHK(dg4_launch_attn(dt, d, t, s));
 
             // s_{l+1} = LN(s_l + a Wo_l), then (DG4_FFN) s_{l+1} <- LN(s_{l+1} + relu(s_{l+1} W1_l) W2_l);

@@ -231,23 +231,22 @@ __global__ void pack_w_kernel(const T* w, int ld, int col0, int n_cols, int k_di
 // the A operand in registers and streams the packed weight tiles.
 // Accumulator element i of a lane sits at row 8*(i/4) + 4*(lane/32) + i%4,
 // column lane%32 of the 32x32 tile.
-template <typename T, int D, bool LN>
+template <typename T, int D>
 __global__ __launch_bounds__(256) void gemm_kernel(dg4_gemm_args p)
 {
     constexpr int E = 16 / sizeof(T);
     constexpr int KC = D / (2 * E);
-    constexpr int NT_LN = D / 32;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int m = lane & 31, kg = lane >> 5;
     // Either every wave takes its own 32 rows and all columns, or (split: wide outputs, few rows,
     // as in a level of the sweep) the four waves of a workgroup share 32 rows and take a quarter
     // of the columns each, which puts four times as many compute units to work.
-    const bool split = !LN && p.split != 0;
+    const bool split = p.split != 0;
     const int64_t r0 = p.row_begin + (split ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wave) * 32;
     constexpr int TS = 32 + E;                    // row stride of a staged 32x32 tile
     constexpr int TPR = 32 / E;                   // 16-byte pieces per row of a tile
-    __shared__ __attribute__((aligned(16))) T tile[LN ? 1 : 4][LN ? 1 : 32 * TS];
+    __shared__ __attribute__((aligned(16))) T tile[4][32 * TS];
     if (r0 >= p.row_end) return;
 
     uint4 a[KC];
@@ -261,16 +260,6 @@ __global__ __launch_bounds__(256) void gemm_kernel(dg4_gemm_args p)
     }
     const uint4* wp = (const uint4*)p.w_packed;
 
-    // rows this lane's accumulator elements belong to
-    int64_t orow[16];
-    bool ok[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int64_t r = r0 + 8 * (i / 4) + 4 * kg + (i % 4);
-        ok[i] = r < p.row_end;
-        orow[i] = ok[i] ? r : p.row_end - 1;
-    }
-
     // The packed weight is one linear stream of 16-byte-per-lane fragments (tile nt, chunk c at
     // nt*KC + c). It is read through a ring of RING fragments requested RING products ahead:
     // with 32 rows per wave a level's kernel has few waves, and each would otherwise wait out
@@ -278,7 +267,6 @@ __global__ __launch_bounds__(256) void gemm_kernel(dg4_gemm_args p)
     // multiple of both RING and KC), so that every register index below is a compile-time constant.
     constexpr int RING = 16;
     constexpr int GROUP = KC > RING ? KC : RING;
-    constexpr int TPG = GROUP / KC;               // column tiles per group
     uint4 ring[RING];
     const int64_t all = (int64_t)(p.n_cols / 32) * KC;
     // this wave's part of the stream: a multiple of GROUP fragments (checked by the launcher)
@@ -287,91 +275,48 @@ __global__ __launch_bounds__(256) void gemm_kernel(dg4_gemm_args p)
 #pragma unroll
     for (int j = 0; j < RING; ++j) ring[j] = wp[(first + j) * 64 + lane];
 
-    if constexpr (!LN) {
-        for (int64_t f0 = first; f0 < total; f0 += GROUP) {
-            f32x16 acc;
+    for (int64_t f0 = first; f0 < total; f0 += GROUP) {
+        f32x16 acc;
 #pragma unroll
-            for (int j = 0; j < GROUP; ++j) {
-                const int c = j % KC;
-                if (c == 0) {
+        for (int j = 0; j < GROUP; ++j) {
+            const int c = j % KC;
+            if (c == 0) {
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-                }
-                Mma<T>::run(a[c], ring[j % RING], acc);
-                if (f0 + j + RING < total) ring[j % RING] = wp[(f0 + j + RING) * 64 + lane];
-                if (c == KC - 1) {
-                    // the 32x32 tile leaves through this wave's own corner of LDS, as 16-byte pieces
-                    // of rows (LDS operations of a wave complete in order: no barrier)
+                for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+            }
+            Mma<T>::run(a[c], ring[j % RING], acc);
+            if (f0 + j + RING < total) ring[j % RING] = wp[(f0 + j + RING) * 64 + lane];
+            if (c == KC - 1) {
+                // the 32x32 tile leaves through this wave's own corner of LDS, as 16-byte pieces
+                // of rows (LDS operations of a wave complete in order: no barrier)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        Elem<T>::store1(tile[wave], (int64_t)(8 * (i / 4) + 4 * kg + (i % 4)) * TS + m, acc[i]);
-                    const int col = (int)(f0 / KC + j / KC) * 32;
-                    T* base = (T*)p.out[col / D] + col % D;
+                for (int i = 0; i < 16; ++i)
+                    Elem<T>::store1(tile[wave], (int64_t)(8 * (i / 4) + 4 * kg + (i % 4)) * TS + m, acc[i]);
+                const int col = (int)(f0 / KC + j / KC) * 32;
+                T* base = (T*)p.out[col / D] + col % D;
 #pragma unroll
-                    for (int q = 0; q < 32 * TPR / 64; ++q) {
-                        const int piece = lane + 64 * q, row = piece / TPR, cc = piece % TPR;
-                        const uint4 v = *(const uint4*)&tile[wave][row * TS + cc * E];
-                        const int64_t r = r0 + row;
-                        if (r < p.row_end) {
-                            const int64_t orr = p.out_scatter ? (int64_t)p.out_scatter[r] : r;
-                            *(uint4*)(base + orr * p.out_stride + cc * E) = v;
-                            if (p.out2) *(uint4*)((T*)p.out2 + r * p.out2_stride + col + cc * E) = v;
-                        }
+                for (int q = 0; q < 32 * TPR / 64; ++q) {
+                    const int piece = lane + 64 * q, row = piece / TPR, cc = piece % TPR;
+                    const uint4 v = *(const uint4*)&tile[wave][row * TS + cc * E];
+                    const int64_t r = r0 + row;
+                    if (r < p.row_end) {
+                        const int64_t orr = p.out_scatter ? (int64_t)p.out_scatter[r] : r;
+                        *(uint4*)(base + orr * p.out_stride + cc * E) = v;
+                        if (p.out2) *(uint4*)((T*)p.out2 + r * p.out2_stride + col + cc * E) = v;
                     }
                 }
-            }
-        }
-    } else {
-        f32x16 acc[NT_LN];
-        static_assert(NT_LN % TPG == 0, "whole groups");
-#pragma unroll
-        for (int g = 0; g < NT_LN / TPG; ++g) {
-#pragma unroll
-            for (int j = 0; j < GROUP; ++j) {
-                const int c = j % KC, nt = g * TPG + j / KC;
-                if (c == 0) {
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[nt][i] = 0.f;
-                }
-                Mma<T>::run(a[c], ring[j % RING], acc[nt]);
-                if (g * GROUP + j + RING < NT_LN * KC) ring[j % RING] = wp[(int64_t)(g * GROUP + j + RING) * 64 + lane];
-            }
-        }
-        // residual, then LayerNorm over each row (no affine, biased variance)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int64_t rr = p.resid_gather ? (int64_t)p.resid_gather[orow[i]] : orow[i];
-            float s1 = 0.f;
-#pragma unroll
-            for (int nt = 0; nt < NT_LN; ++nt) {
-                acc[nt][i] += Elem<T>::load1(p.resid, rr * p.resid_stride + nt * 32 + m);
-                s1 += acc[nt][i];
-            }
-            const float mean = sum_over_32_lanes(s1) * (1.0f / D);
-            float s2 = 0.f;
-#pragma unroll
-            for (int nt = 0; nt < NT_LN; ++nt) { const float t = acc[nt][i] - mean; s2 = fmaf(t, t, s2); }
-            const float rstd = rsqrtf(sum_over_32_lanes(s2) * (1.0f / D) + p.ln_eps);
-            if (!ok[i]) continue;
-            const int64_t orr = p.out_scatter ? (int64_t)p.out_scatter[orow[i]] : orow[i];
-#pragma unroll
-            for (int nt = 0; nt < NT_LN; ++nt) {
-                const float y = (acc[nt][i] - mean) * rstd;
-                Elem<T>::store1(p.out[0], orr * p.out_stride + nt * 32 + m, y);
-                if (p.out2) Elem<T>::store1(p.out2, orow[i] * p.out2_stride + nt * 32 + m, y);
             }
         }
     }
 }
 
-// gemm_kernel<.., LN = true> for launches with few rows: the four waves of a workgroup share 32 rows
-// and take a quarter of the D output columns each (four times as many compute units at work, a
-// quarter of the weight stream per wave); the LayerNorm sums are completed through LDS.
+// The product with residual + LayerNorm behind it: the four waves of a workgroup share 32 rows
+// and take a quarter of the D output columns each; the LayerNorm sums are completed through LDS.
 // KV: the normalised rows also go, rounded to T, through LDS into a second product with the packed
 // [D, 2D] weight p.kv_w_packed, each wave taking a quarter of its 2D columns (the K | V rows of the
 // gates of a one-layer sweep, otherwise a launch of their own).
 // AW > 0: the rows' operand is not read from memory but computed here, the attention of the 32
-// rows over neighbour rows of width AW (attend_row, two or four rows per lane group, through LDS
+// rows over neighbour rows of width AW (attend_row, one, two or four rows per lane group, through LDS
 // into the operand layout): attention, output projection, LayerNorm and K | V in one launch.
 // fp32 / 256 is the largest: as one loop over its 64 fragments the product was not unrolled and read the rows' operand from
 // scratch memory (528 bytes a lane), and with 16 fragments ahead only one workgroup fitted a compute unit. As two loops,
@@ -383,7 +328,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 && D == 256 ? 2 : 1) void gemm_
     constexpr int E = 16 / sizeof(T);
     constexpr int KC = D / (2 * E);
     constexpr int NTW = D / 32 / 4;               // column tiles per wave
-    constexpr int RING = sizeof(T) == 4 && D == 256 ? 8 : 16;
+    constexpr int RING = (sizeof(T) == 4) == (D == 256) ? 8 : 16;        // (bf16 / 128: a wave's columns are eight fragments)
     constexpr int GROUP = KC > RING ? KC : RING;
     static_assert((NTW * KC) % GROUP == 0, "whole groups per wave");
     __shared__ float part[2][4][32];
@@ -563,45 +508,36 @@ int launch_gemm_t(const dg4_gemm_args& a, const dg4_attn_args* att, hipStream_t 
     if (a.n_cols % 32 != 0 || frags % GROUP != 0) return hipErrorInvalidValue;
     if (a.epilogue) {
         if (a.n_cols != D) return hipErrorInvalidValue;
-        constexpr bool can_split = ((D / 32 / 4) * KC) % GROUP == 0 && (D / 32) % 4 == 0;
-        // (always the same kernel for a given shape, whatever the number of rows: the two sum the
-        // LayerNorm statistics in different orders, and the embeddings must not depend on how the
-        // rows were cut into launches)
-        if constexpr (can_split) {
-            const dim3 g32((unsigned)((rows + 31) / 32));
-            const dg4_attn_args none{};
-            const int aw = att ? att->ell_w : 0;
-            if (att && (att->row_begin != a.row_begin || att->row_end != a.row_end)) return hipErrorInvalidValue;
+        const dim3 g32((unsigned)((rows + 31) / 32));
+        const dg4_attn_args none{};
+        const int aw = att ? att->ell_w : 0;
+        if (att && (att->row_begin != a.row_begin || att->row_end != a.row_end)) return hipErrorInvalidValue;
 #define DG4_LAUNCH_LN(KV_, AW_) hipLaunchKernelGGL((gemm_ln_split_kernel<T, D, KV_, AW_>), g32, dim3(256), 0, s, a, att ? *att : none)
-            if (a.kv_out) {
-                switch (aw) {
-                case 0: DG4_LAUNCH_LN(true, 0); break;
-                case 4: DG4_LAUNCH_LN(true, 4); break;
-                case 8: DG4_LAUNCH_LN(true, 8); break;
-                case 16: DG4_LAUNCH_LN(true, 16); break;
-                default: return hipErrorInvalidValue;
-                }
-            } else {
-                switch (aw) {
-                case 0: DG4_LAUNCH_LN(false, 0); break;
-                case 4: DG4_LAUNCH_LN(false, 4); break;
-                case 8: DG4_LAUNCH_LN(false, 8); break;
-                case 16: DG4_LAUNCH_LN(false, 16); break;
-                default: return hipErrorInvalidValue;
-                }
+        if (a.kv_out) {
+            switch (aw) {
+            case 0: DG4_LAUNCH_LN(true, 0); break;
+            case 4: DG4_LAUNCH_LN(true, 4); break;
+            case 8: DG4_LAUNCH_LN(true, 8); break;
+            case 16: DG4_LAUNCH_LN(true, 16); break;
+            default: return hipErrorInvalidValue;
             }
-#undef DG4_LAUNCH_LN
         } else {
-            if (a.kv_out || att) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((gemm_kernel<T, D, true>), dim3(grid), dim3(256), 0, s, a);
+            switch (aw) {
+            case 0: DG4_LAUNCH_LN(false, 0); break;
+            case 4: DG4_LAUNCH_LN(false, 4); break;
+            case 8: DG4_LAUNCH_LN(false, 8); break;
+            case 16: DG4_LAUNCH_LN(false, 16); break;
+            default: return hipErrorInvalidValue;
+            }
         }
+#undef DG4_LAUNCH_LN
     } else {
         if (a.out2 && a.n_cols != D) return hipErrorInvalidValue;
         dg4_gemm_args b = a;
         // few rows (less than two workgroups per compute unit the plain way): split the columns over the waves
         b.split = (a.n_cols / 32) % 4 == 0 && (frags / 4) % GROUP == 0 && rows < 128 * 512 ? 1 : 0;
         if (b.split) grid = (unsigned)((rows + 31) / 32);
-        hipLaunchKernelGGL((gemm_kernel<T, D, false>), dim3(grid), dim3(256), 0, s, b);
+        hipLaunchKernelGGL((gemm_kernel<T, D>), dim3(grid), dim3(256), 0, s, b);
     }
     return hipGetLastError();
 }
@@ -962,14 +898,6 @@ int dg4_launch_struct_encode(int dtype, int hidden, const void* x, const int32_t
     return hidden == 128 ? launch_struct_encode_t<uint16_t, 128>(x, feat, emb, out, n, s) : launch_struct_encode_t<uint16_t, 256>(x, feat, emb, out, n, s);
 }
 
-// shapes whose epilogue kernel can carry the K | V product (gemm_ln_split_kernel)
-bool dg4_gemm_fuses_kv(int dtype, int hidden)
-{
-    const int e = dtype == DG4_F32 ? 4 : 8;
-    const int kc = hidden / (2 * e), group = kc > 16 ? kc : 16;
-    return (hidden / 32) % 4 == 0 && ((hidden / 32 / 4) * kc) % group == 0;
-}
-
 int dg4_launch_attn(int dtype, int hidden, const dg4_attn_args& a, hipStream_t s)
 {
     if (dtype == DG4_F32) return hidden == 128 ? launch_attn_w<float, 128>(a, s) : launch_attn_w<float, 256>(a, s);
@@ -1007,8 +935,7 @@ int dg4_launch_gemm(int dtype, int hidden, const dg4_gemm_args& a, hipStream_t s
 }
 
 // The epilogue product with its rows' operand computed in the same launch: the attention `att`
-// (same row range, neighbour rows of width 4, 8 or 16) instead of a.a. Shapes for which
-// dg4_gemm_fuses_kv() holds.
+// (same row range, neighbour rows of width 4, 8 or 16) instead of a.a.
 int dg4_launch_attn_gemm(int dtype, int hidden, const dg4_attn_args& att, const dg4_gemm_args& a, hipStream_t s)
 {
     if (!a.epilogue) return hipErrorInvalidValue;
