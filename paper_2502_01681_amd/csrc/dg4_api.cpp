@@ -77,20 +77,21 @@ bool heads_config(const dg4_layer_cfg* c)
 // (bf16 / 256). There the line is twice as high, which is no crossing: the kernel is still ahead at 3038, the widest
 // that was measured, and up to there wider circuits give that away. Where the other path is level-by-level launches
 // (bf16 / 128, fp32 / 256, feed-forward on cones of more than three hops), four times: fp32 / 256, one layer, two hops
-// 1.08 at 1708, 0.97 at 1981 (with feed-forward 1.20, 1.04; three hops 1.16, 1.04). For one layer in bf16 / 128 over cones of
-// up to three hops twice (2048 gates): 1.64 at 1127, 1.23 at 1640, 1.03 at 2186, 0.93 at 2523, 0.79 at 3153 (with
-// feed-forward 1.54, 1.18, 0.97, 0.87, 0.74; three hops 1.79, 1.34, 1.13, 1.01, 0.86), but not under a caller's deeper
-// levelling, whose levels the launches may have to follow. (Several layers cross later: four layers 2.16 at 2270, 1.72 at
-// 3150, 0.93 at 3940; twelve with feed-forward 1.51, 1.21, 0.69.) One layer over two hops in bf16 / 256 without
-// feed-forward has a kernel of its own.
+// 1.08 at 1708, 0.97 at 1981 (with feed-forward 1.20, 1.04; three hops 1.16, 1.04); bf16 / 128, four layers 2.16 at 2270,
+// 1.72 at 3150, 0.93 at 3940, twelve with feed-forward 1.51, 1.21, 0.69. One layer of bf16 / 128 over cones of up to three
+// hops crosses lower: 1.23 at 1640, 1.03 at 2186, 0.93 at 2523, 0.79 at 3153 (with feed-forward 0.97, 0.87, 0.74 at the last
+// three; three hops 1.13, 1.01, 0.86). It stays on this line too, because the line must be the same under every levelling
+// (the paths round differently, and the embeddings may not), and there launches lose: they follow the levels of a caller's
+// deeper levelling, as far as the graph was built on the GPU or the sweep covers a part of it. 2811 gates per level of the
+// circuit's own, this kernel against launches: 199 and 176 us; three levels for each 203 and 406, twenty 208 and 2168.
+// One layer over two hops in bf16 / 256 without feed-forward has a kernel of its own.
 bool heads_route(const dg4_layer_cfg* c, const dg4_graph* g)
 {
     // (without marks the nodes are copies in many shallow components: never narrow)
     if ((c->flags & DG4_PER_LEVEL) || !g->marks || !heads_config(c)) return false;
     const bool ffn = (c->flags & DG4_FFN) != 0;
     const bool streamed = dg4_flow_supports(c->dtype, c->hidden, 8) && (!ffn || c->hops <= 3);
-    const bool small_rows = c->dtype == DG4_BF16 && c->hidden == 128 && c->hops <= 3 && c->n_layers == 1 && !dg4_levels_deeper(g);
-    return dg4_dependency_width(g) <= (int64_t)dg4_head_groups(c->heads) * DG4_HEADS_ROWS * (streamed ? (c->hops >= 6 ? 2 : 1) : small_rows ? 2 : 4);
+    return dg4_dependency_width(g) <= (int64_t)dg4_head_groups(c->heads) * DG4_HEADS_ROWS * (!streamed ? 4 : c->hops >= 6 ? 2 : 1);
 }
 
 LayerPlan plan_layer(const dg4_layer_cfg* c, const dg4_graph* g)

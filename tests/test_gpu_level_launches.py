@@ -44,30 +44,51 @@ def test_level_by_level(hidden, dtype, n_pi, n_and, cap, hops, layers, ffn):
     assert torch.equal(H, cut)
 
 
-@pytest.mark.parametrize("n_pi,n_and,ffn", [(2_000, 4_000, False), (2_000, 4_000, True), (2_300, 4_700, False), (2_300, 4_700, True)])
-@pytest.mark.parametrize("hops", [2, 3])
-def test_one_layer_bf16_128_on_both_sides_of_2048_gates_per_level(n_pi, n_and, ffn, hops):
-    """Below: the heads of a tile over compute units; above: level-by-level launches, unless a caller's levelling is deeper than
-    the circuit. Each against the oracle, and cut in two to the same bits."""
+@pytest.mark.parametrize("n_pi,n_and,launches", [(2_300, 4_700, False), (4_000, 8_200, False), (4_200, 8_200, True)])
+@pytest.mark.parametrize("hops,ffn", [(2, False), (2, True), (3, False), (3, True)])
+def test_one_layer_bf16_128_is_the_same_bits_under_every_levelling(n_pi, n_and, launches, hops, ffn):
+    """Up to 4096 gates per level the heads of a tile over compute units, above level-by-level launches: by the circuit, not by
+    the levelling, so that a caller's deeper one, host- or device-built, whole or cut in two, changes no bit."""
     w = synth.make(synth.Config("sides", 23, n_pi, n_and, 3_000, 0.5, 2, 128, 4, hops, 1, "bf16"))
     c = w.cfg
     fw = synth.ffn_weights(c) if ffn else None
     X, W = to_dev(w.x, c.dtype), device_weights(w, c.dtype)
     if ffn:
         W = [lw + (to_dev(fw[0][l], c.dtype), to_dev(fw[1][l], c.dtype)) for l, lw in enumerate(W)]
-    cfg = cfg_of(c, ffn=ffn)
+    cfg = cfg_of(c, ffn=ffn, time_sweep=True)
+    edges = [torch.from_numpy(a).cuda() for a in (w.edge_src, w.edge_dst, w.edge_inv)]
+
+    def run(g, cuts=((0, None),), cfg=cfg):
+        ws = torch.full((dg4.dg4_layer_workspace_bytes(cfg, g),), 0xFF, dtype=torch.uint8, device="cuda")
+        H = torch.full_like(X, float("nan"))
+        for begin, end in cuts:
+            dg4.dg4_layer_fwd(cfg, g, X, W, H, begin, end, workspace=ws)
+        torch.cuda.synchronize()
+        dg4.dg4_layer_status(cfg, g, ws)
+        return H
+
+    own = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops)
+    width = c.n_nodes // own.n_levels
+    assert (width > 4096) == launches
+    print(f"one layer bf16 128: {width} gates per level, hops {hops}, ffn {ffn}", flush=True)
+    H = run(own)
+    if launches:            # (no persistent kernel ran: nothing was timed)
+        with pytest.raises(dg4.DG4Error):
+            dg4.dg4_sweep_elapsed_ms()
+        assert torch.equal(H, run(own, cfg=cfg_of(c, ffn=ffn, per_level=True)))
+    else:
+        assert dg4.dg4_sweep_elapsed_ms() > 0
     og = oracle.build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops)
     kw = dict(w1=fw[0], w2=fw[1]) if ffn else {}
     ref = oracle.layer_fwd(og, w.x, w.wqkv, w.wo, w.rel_bias, c.heads, store=c.dtype, **kw)
-    hint = (3 * og.level).astype(np.int32)
-    for deeper in (None, hint):
-        g = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops, deeper)
-        print(f"one layer bf16 128: {c.n_nodes // og.n_levels} gates per level, hops {hops}, ffn {ffn}, deeper {deeper is not None}", flush=True)
-        ws = torch.full((dg4.dg4_layer_workspace_bytes(cfg, g),), 0xFF, dtype=torch.uint8, device="cuda")
-        H, cut = torch.full_like(X, float("nan")), torch.full_like(X, float("nan"))
-        dg4.dg4_layer_fwd(cfg, g, X, W, H, workspace=ws)
-        assert row_rel_err(to_np(H), ref).max() <= TOL[c.dtype]
-        ws.fill_(0xFF)
-        for begin, end in ((0, 1), (1, None)):
-            dg4.dg4_layer_fwd(cfg, g, X, W, cut, begin, end, workspace=ws)
-        assert torch.equal(H, cut)
+    assert row_rel_err(to_np(H), ref).max() <= TOL[c.dtype]
+    level = og.level
+    for hint in (3 * level, np.where(level > 0, 5 * level + np.arange(c.n_nodes) % 5, 0)):
+        hint = np.ascontiguousarray(hint.astype(np.int32))
+        on_host = dg4.dg4_build_levels(c.n_nodes, w.edge_src, w.edge_dst, w.edge_inv, hops, hint)
+        on_gpu = dg4.dg4_build_levels_device(c.n_nodes, *edges, hops, torch.from_numpy(hint).cuda())
+        mid = on_host.n_levels // 2
+        assert torch.equal(H, run(on_host)) and torch.equal(H, run(on_gpu))
+        assert torch.equal(H, run(on_host, ((0, mid), (mid, None)))) and torch.equal(H, run(on_gpu, ((0, 1), (1, None))))
+    assert torch.equal(H, run(dg4.dg4_build_levels_device(c.n_nodes, *edges, hops)))
+    assert torch.equal(H, run(own, ((0, 1), (1, None))))
