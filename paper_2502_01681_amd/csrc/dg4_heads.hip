@@ -257,7 +257,11 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
     float* att = (float*)(heads_smem + LDS::off_att);            // [part][32] weighted sums, then [part][2] maximum, denominator
     int* ctl = (int*)(heads_smem + LDS::off_ctl); // this tile's and the next one's {first position, rows}, [8] abort word, [12], [13] place in a group
     float* biases = (float*)(ctl + 16);           // [layers][4] of this head
-    // neighbour rows: what is no source (padding, the gate itself) holds relation 0 and the row past the store's end
+    // Neighbour rows: what is no source (padding, the gate itself) holds relation 0 and the row past the store's end. Narrow
+    // rows of one layer lie there as the table has them: they are read once, and rewriting them is on every tile's way to its
+    // sources (fp32 / 256, two hops, 30,300 gates: 3.242 -> 3.210 ms). Several layers read them several times (as the table has
+    // them: twelve layers fp32 / 128 5.88 -> 5.94 ms).
+    constexpr bool AS_STORED = W != 0 && ONE;
     uint32_t* ent = (uint32_t*)(heads_smem + LDS::off_ent);
     const int tile_rows = W ? HR : p.tile_rows;
     const int ell_w = W ? W : LDS::row_words(p.ell_w, tile_rows);
@@ -561,11 +565,11 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
             *(uint4*)&resid[row * YS + c * E] = *((const uint4*)((const T*)p.x + id * D) + c);
         }
         const auto no_source = [&](uint32_t e) __attribute__((always_inline)) { return e == DG4_ELL_PAD || (e >> 30) == 0 ? (uint32_t)N : e; };
-        auto put4 = [&](int i, const uint4& e) __attribute__((always_inline)) {
-            ((uint4*)ent)[i] = make_uint4(no_source(e.x), no_source(e.y), no_source(e.z), no_source(e.w));
-        };
         if constexpr (W != 0) {
-            for (int i = tid; i < rows * (W / 4); i += HT) put4(i, ((const uint4*)(p.ell + p0 * (int64_t)W))[i]);
+            for (int i = tid; i < rows * (W / 4); i += HT) {
+                const uint4 e = ((const uint4*)(p.ell + p0 * (int64_t)W))[i];
+                ((uint4*)ent)[i] = AS_STORED ? e : make_uint4(no_source(e.x), no_source(e.y), no_source(e.z), no_source(e.w));
+            }
         } else {
             // entry i of a round lies where lane group i % SG finds its (i / SG)-th: a group reads its eight entries as two
             // 16-byte words, and the groups of a row request ask for entries side by side
@@ -615,6 +619,7 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
         auto rows_of_layer = [&](int l) __attribute__((always_inline)) {
             return row_buffer((const T*)p.kv + ((int64_t)l * C + slice) * N * 64, 64 * sizeof(T), (uint32_t)N);
         };
+        auto is_source = [&](uint32_t e) __attribute__((always_inline)) { return !(AS_STORED && e == DG4_ELL_PAD) && (e >> 30) != 0; };
         // (An entry that is no source asks for the row past the end: zeros, no request. K and V of an entry back to back: they
         // share a cache line, which is gone from the L1 when all K rows of a round are asked for first. Narrow rows have one to
         // four entries per lane group and are left to the compiler: kept apart they cost one layer in bf16 / 128 3 %, 1.463 ->
@@ -624,17 +629,17 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
             const uint32_t off = (uint32_t)sub_of() * 16u;
 #pragma unroll
             for (int j = 0; j < CH; ++j) {
-                k4[j] = row_load16(kvb, en[j] & 0x3FFFFFFFu, off);
-                v4[j] = row_load16(kvb, en[j] & 0x3FFFFFFFu, off + (uint32_t)(32 * sizeof(T)));
+                const uint32_t row = AS_STORED && !is_source(en[j]) ? (uint32_t)N : en[j] & 0x3FFFFFFFu;
+                k4[j] = row_load16(kvb, row, off);
+                v4[j] = row_load16(kvb, row, off + (uint32_t)(32 * sizeof(T)));
                 if constexpr (W == 0) __builtin_amdgcn_sched_barrier(0);
             }
         };
-        auto is_source = [&](uint32_t e) __attribute__((always_inline)) { return (e >> 30) != 0; };
         // (W != 0) the sources of a layer
         auto request_first = [&](int l) __attribute__((always_inline)) {
             const int r = gate_of(), grp = group_of();
 #pragma unroll
-            for (int j = 0; j < CH; ++j) en[j] = r < rows ? ent[r * W + grp + SG * j] : (uint32_t)N;
+            for (int j = 0; j < CH; ++j) en[j] = r < rows ? ent[r * W + grp + SG * j] : AS_STORED ? DG4_ELL_PAD : (uint32_t)N;
             request(l);
         };
         {
@@ -658,7 +663,7 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
                             const int i = next + HT * q;
                             const uint32_t e = i < count ? ent[i] : 0u;
                             seen[q] = 1u;
-                            if (e >> 30) seen[q] = __hip_atomic_load(flags + (e & 0x3FFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            if (is_source(e)) seen[q] = __hip_atomic_load(flags + (e & 0x3FFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         }
 #pragma unroll
                         for (int q = 0; q < Q; ++q) ok = ok && seen[q] != 0u;
