@@ -284,6 +284,10 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
     auto next_phase = [&]() __attribute__((always_inline)) { phase(tid); __asm__ volatile("" : "+s"(slice)); };
     const int L = ONE ? 1 : p.n_layers;
     const int64_t N = p.n_rows;
+    // One layer over wide rows asks for Wo behind the gathers (loads complete in order, and nothing but the gathers is in flight
+    // then): with feed-forward, eight hops, 15,300 gates, bf16 / 128 841 -> 828 us, bf16 / 256 1267 -> 1249, fp32 / 256 2257 ->
+    // 2225. Not with feed-forward in fp32 / 128: 1074 -> 1082.
+    const bool wo_late = W == 0 && (ONE || (L == 1 && !(sizeof(T) == 4 && D == 128)));
     uint32_t* flags = p.flags + (int64_t)slice * N;
 
     // phase timers (DG4_PROFILE): ticket, first projection + wait, attention + exchange, output projection + LayerNorm,
@@ -645,7 +649,7 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
         {
             next_phase();
             project(resid, 0);
-            if (W || !ONE) fill_wo(0);
+            if (!wo_late) fill_wo(0);
             next_phase();
             // ---- the sources of the tile's gates must be published (in this slice)
             {
@@ -832,7 +836,7 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
                     put_word(xa + (int64_t)r * WPR + slice * WPS + w,
                              sizeof(T) == 4 ? __float_as_uint(v0 * rz) : pack_bf16x2(v0 * rz, v1 * rz), tag);
                 }
-                if (!W && ONE) fill_wo(0);        // (not before the gathers)
+                if (wo_late) fill_wo(0);
                 // ---- ... and theirs come in
                 collect(xa, rows * WPR, tag, std::integral_constant<int, HR * WPR / HT>{}, [&](int i, uint32_t data) __attribute__((always_inline)) {
                     *(uint32_t*)((unsigned char*)(ybuf + (i / WPR) * YS) + (i % WPR) * 4) = data;
