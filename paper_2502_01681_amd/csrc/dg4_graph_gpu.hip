@@ -518,8 +518,9 @@ inline void sort_pairs(const uint32_t* keys, const int32_t* vals, uint32_t* keys
     }
 }
 
-// Device memory of one call: carved out of at most two allocations (the tables sized by the node
-// count, then those sized by the number of neighbour entries), released when the call returns.
+// Device memory of one call, released when it returns: carved out of one allocation for what goes by the node count, then one
+// for the neighbour rows (cones of more than three hops: one per hop; a partition: three more). What an allocation has
+// no room for gets its own, which costs about 10 us, so everything is taken from the one that is sized for it.
 struct Arena {
     std::vector<void*> blocks;
     char* cur = nullptr;
@@ -626,8 +627,8 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
             return DG4_OK;
         }
         Arena arena;
-        // everything sized by the node count in one allocation (about 140 bytes a node, plus the
-        // sort's and the scan's own scratch, which are small)
+        // everything sized by the node count in one allocation (up to 153 bytes a node, plus 8 a level and the scan's
+        // scratch, which is small)
         if (!arena.reserve((size_t)n * 160 + (16u << 20))) return DG4_ENOMEM;
         GPU_ALLOC(fin, int32_t, 2 * (size_t)n, false);
         GPU_ALLOC(finv, uint8_t, 2 * (size_t)n, true);
@@ -692,6 +693,22 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
         GPU_ALLOC(level_ptr, int64_t, (size_t)n_ptr, false);
         hipLaunchKernelGGL(level_ptr_kernel, dim3(blocks_for(n_ptr)), dim3(256), 0, s, n, sorted_level, n_ptr, level_ptr);
 
+        // what the processing order and the fanout counts need: before the rows, whose allocation replaces this one
+        int32_t* sweep = nullptr;
+        int32_t* pos = nullptr;
+        uint8_t* soon = nullptr;
+        uint32_t* key = nullptr;
+        if (stride == 0) {
+            soon = arena.get<uint8_t>((size_t)n, true, s);
+            key = arena.get<uint32_t>((size_t)n, false, s);
+            sweep = arena.get<int32_t>((size_t)n, false, s);
+            pos = arena.get<int32_t>((size_t)n, false, s);
+            if (!soon || !key || !sweep || !pos) return DG4_ENOMEM;
+        }
+        GPU_ALLOC(out_and, int32_t, (size_t)n, true);
+        GPU_ALLOC(out_not, int32_t, (size_t)n, true);
+        GPU_ALLOC(inverter, uint8_t, (size_t)n, true);
+
         // cones
         GPU_ALLOC(cnt, int64_t, (size_t)n + 1, true);
         GPU_ALLOC(nbr_ptr, int64_t, (size_t)n + 1, false);
@@ -741,14 +758,7 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
         // gates, by the latest fanin's position and then by (level, read late), from (level, id) positions first and from
         // those of the first result after that: it tells apart what the first result already has in its place, which
         // is the part of the order that a sweep's time depends on.
-        int32_t* sweep = nullptr;
-        int32_t* pos = nullptr;
         if (stride == 0) {
-            GPU_ALLOC(soon, uint8_t, (size_t)n, true);
-            GPU_ALLOC(key, uint32_t, (size_t)n, false);
-            sweep = arena.get<int32_t>((size_t)n, false, s);
-            pos = arena.get<int32_t>((size_t)n, false, s);
-            if (!sweep || !pos) return DG4_ENOMEM;
             int pos_bits = 1, part_bits = 1;
             while ((n >> pos_bits) != 0) ++pos_bits;          // keys 0 .. n
             while (((2 * (int64_t)h_max + 1) >> part_bits) != 0) ++part_bits;
@@ -837,9 +847,6 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
         g->nnz = nnz;
 
         // fanout counts of the structural encoding
-        GPU_ALLOC(out_and, int32_t, (size_t)n, true);
-        GPU_ALLOC(out_not, int32_t, (size_t)n, true);
-        GPU_ALLOC(inverter, uint8_t, (size_t)n, true);
         hipLaunchKernelGGL(fanout_kernel, dim3(nb), dim3(256), 0, s, n, fin, finv, deg, out_and, out_not, inverter);
         hipLaunchKernelGGL(add_inverter_kernel, dim3(nb), dim3(256), 0, s, n, out_not, inverter);
         GPU_CHECK(hipGetLastError());
