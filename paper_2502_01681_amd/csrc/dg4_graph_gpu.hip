@@ -699,7 +699,7 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
         uint8_t* soon = nullptr;
         uint32_t* key = nullptr;
         if (stride == 0) {
-            soon = arena.get<uint8_t>((size_t)n, true, s);
+            soon = arena.get<uint8_t>((size_t)n, false, s);
             key = arena.get<uint32_t>((size_t)n, false, s);
             sweep = arena.get<int32_t>((size_t)n, false, s);
             pos = arena.get<int32_t>((size_t)n, false, s);
@@ -754,11 +754,21 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
             if (ptr_prev != nbr_ptr)             // the last hop's pointers, where the copies below expect them
                 GPU_CHECK(hipMemcpyAsync(nbr_ptr, ptr_prev, ((size_t)n + 1) * sizeof(int64_t), hipMemcpyDeviceToDevice, s));
         }
-        // Processing order: where the host walks the levels one after the other (2.1 ms for 102 K gates), two stable sorts over all
-        // gates, by the latest fanin's position and then by (level, read late), from (level, id) positions first and from
-        // those of the first result after that: it tells apart what the first result already has in its place, which
-        // is the part of the order that a sweep's time depends on.
-        if (stride == 0) {
+        // Processing order, in place of the host's (dg4_graph_ensure_device), which walks the levels one after the other: two
+        // stable sorts over all gates, by the latest fanin's position and then by (level, read late), from (level, id)
+        // positions first and from those of the first result after that. The host orders by final positions, so the two
+        // differ inside the runs of a level; no result depends on either.
+        // The sorts take 150 us whatever the size, the host about 12 ns a gate and half a nanosecond a row entry, unless it
+        // makes a list schedule as well: that runs beside it on another thread and takes longer. A new circuit and its first
+        // sweep, here against on the host, ms: no list schedule, two hops 0.96 and 0.87 at 6400 gates, 1.04 and 1.10 at
+        // 12,800, 1.09 and 1.35 at 21,300; three hops 1.65 and 1.54 at 3200, 1.82 and 1.91 at 9600, 1.63 and 2.17 at
+        // 26,600; five hops 1.16 and 1.11 at 2200, 1.29 and 1.32 at 4300. With a list schedule 1.34 and 1.18 at 1100,
+        // 3.49 and 3.34 at 26,600, 13.5 and 13.3 at 106,000.
+        // (as dg4_graph_ensure_device decides; fanins are kept for a levelling deeper than the circuit's)
+        const bool listed = hops <= 2 && (!g->fanin.empty() || !dg4_sweeps_by_level(g.get(), false));
+        const bool order_here = stride == 0 && !listed && 24 * n + nnz >= (1 << 18);
+        if (order_here) {
+            GPU_CHECK(hipMemsetAsync(soon, 0, (size_t)n, s));
             int pos_bits = 1, part_bits = 1;
             while ((n >> pos_bits) != 0) ++pos_bits;          // keys 0 .. n
             while (((2 * (int64_t)h_max + 1) >> part_bits) != 0) ++part_bits;
@@ -868,13 +878,13 @@ int build_device(int64_t n, int64_t e, const int32_t* es, const int32_t* ed, con
             g->stage.resize((size_t)n);
             GPU_CHECK(hipMemcpyAsync(g->stage.data(), stage, (size_t)n * 4, hipMemcpyDeviceToHost, s));
         }
-        if (sweep) {
+        if (order_here) {
             g->sweep_order.resize((size_t)n);
             GPU_CHECK(hipMemcpyAsync(g->sweep_order.data(), sweep, (size_t)n * 4, hipMemcpyDeviceToHost, s));
             GPU_CHECK(hipMemcpyAsync(g->pos.data(), pos, (size_t)n * 4, hipMemcpyDeviceToHost, s));
         }
         GPU_CHECK(hipStreamSynchronize(s));
-        if (!sweep)
+        if (!order_here)
             for (int64_t p = 0; p < n; ++p) g->pos[(size_t)g->order[(size_t)p]] = (int32_t)p;
         *out = g.release();
         return DG4_OK;
