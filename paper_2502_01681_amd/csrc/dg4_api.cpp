@@ -80,10 +80,15 @@ bool heads_config(const dg4_layer_cfg* c)
 // 1.08 at 1708, 0.97 at 1981 (with feed-forward 1.20, 1.04; three hops 1.16, 1.04); bf16 / 128, four layers 2.16 at 2270,
 // 1.72 at 3150, 0.93 at 3940, twelve with feed-forward 1.51, 1.21, 0.69. One layer of bf16 / 128 over cones of up to three
 // hops crosses lower: 1.23 at 1640, 1.03 at 2186, 0.93 at 2523, 0.79 at 3153 (with feed-forward 0.97, 0.87, 0.74 at the last
-// three; three hops 1.13, 1.01, 0.86). It stays on this line too, because the line must be the same under every levelling
-// (the paths round differently, and the embeddings may not), and there launches lose: they follow the levels of a caller's
-// deeper levelling, as far as the graph was built on the GPU or the sweep covers a part of it. 2811 gates per level of the
-// circuit's own, this kernel against launches: 199 and 176 us; three levels for each 203 and 406, twenty 208 and 2168.
+// three; three hops 1.13, 1.01, 0.86). Feed-forward, one layer, k = 8 (170 sources): fp32 / 128 1.80 at 1205, 1.47 at 1748,
+// 1.22 at 2543; bf16 / 256 1.89 at 571, 1.37 at 921, 1.13 at 1209; bf16 / 128 1.75, 1.46, 1.20; fp32 / 256 2.62, 1.88, 1.54;
+// k = 4 (20 sources) 1.97, 1.53, 1.13; 2.01, 1.39, 1.06; 1.66, 1.22, 0.88; 2.88, 1.93, 1.49; shallow circuits whose
+// deep cones hold six gates 0.86 at 3000, 0.81 at 1500, 0.73 at 3000, 1.14 at 1500. With four layers all but those are 1.4
+// and more. What crosses lower than the line stays on it, because the line must be the same under every levelling (the
+// paths round differently, and the embeddings may not), and there launches lose: they follow the levels of a caller's
+// deeper levelling, as far as the graph was built on the GPU or the sweep covers a part of it. One layer in bf16 / 128 at 2811
+// gates per level of the circuit's own, this kernel against launches: 199 and 176 us; three levels for each 203 and 406,
+// twenty 208 and 2168.
 // One layer over two hops in bf16 / 256 without feed-forward has a kernel of its own.
 bool heads_route(const dg4_layer_cfg* c, const dg4_graph* g)
 {
