@@ -371,7 +371,7 @@ int dg4_layer_profile(const dg4_layer_cfg* cfg, const dg4_graph* g, const void* 
  * Tracing aid: device time in milliseconds of the persistent sweep kernel of the most recent
  * dg4_layer_fwd (of any thread) that ran one with DG4_TIME_SWEEP in cfg->flags (two events recorded
  * on the caller's stream around that one kernel). Waits for the kernel. EINVAL if no such call
- * has been made.
+ * has been made, or if a later call with DG4_TIME_SWEEP ran level by level.
  */
 int dg4_sweep_elapsed_ms(float* ms);
 

@@ -853,7 +853,8 @@ int dg4_graph_ensure_device(dg4_graph* g)
             try { body(); } catch (const std::bad_alloc&) { rc_job[slot] = DG4_ENOMEM; }
         };
         auto job_levels = [&]() { guarded(0, [&]() {
-            // (whole cone rows of a graph built on the GPU: ordered there, by the same rule)
+            // (whole cone rows of a graph that was ordered on the GPU: there by two looks, so not the order below inside the runs
+            // of a level)
             if (!g->sweep_order.empty()) { std::copy(g->sweep_order.begin(), g->sweep_order.end(), sweep.begin()); return; }
             // (whole cones: the first reader of a gate is a direct one and its latest source a direct fanin, as
             // levels rise along every edge; rows cut by a partition may lack a fanin and are looked at whole)

@@ -1,9 +1,9 @@
 // Graph analysis of paper Section 3.2 on the device, behind dg4_build_levels_device: validation,
 // fanin table, logic levels (Eq. 1) by rounds over the fanin table, the (level, id) order by a
 // stable radix sort (this file's own, like its prefix sum), cone_k rows with relation codes by a per-gate backward search, and the fanout
-// counts of Eq. 2. Integer work throughout: every table equals the host builder's bit for bit
-// (nothing here depends on the order in which atomics land: the fanin slot a source takes is not
-// observable in any output).
+// counts of Eq. 2. Integer work throughout: every table that dg4_graph_array hands out equals the host builder's bit for
+// bit, and nothing depends on the order in which atomics land (the fanin slot a source takes is not observable in any
+// output). The processing order inside the levels, which no result depends on, is one of its own.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -557,8 +557,8 @@ __global__ void position_kernel(int64_t n, const int32_t* order, int32_t* pos)
     if (r < n) pos[order[r]] = (int32_t)r;
 }
 
-// The processing order inside the levels, for whole cone rows (dg4_graph_ensure_device has its rule): gates that some gate at
-// most two levels up reads first, each part by the position of the latest fanin.
+// The processing order inside the levels, for whole cone rows (dg4_graph_ensure_device says why): gates that some gate at
+// most two levels up reads first, each part by the position of the latest fanin, as far as two looks tell it.
 __global__ void read_soon_kernel(int64_t n, const int32_t* fin, const int32_t* deg, const int32_t* level, uint8_t* soon)
 {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -580,7 +580,7 @@ __global__ void latest_fanin_kernel(int64_t n, const int32_t* order, const int32
 __global__ void level_part_kernel(int64_t n, const int32_t* order, const int32_t* level, const uint8_t* soon, uint32_t* key)
 {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < n) key[r] = 2u * (uint32_t)level[order[r]] + (soon[order[r]] ? 0u : 1u);      // (below 2^31: n < 2^30 - 1)
+    if (r < n) key[r] = 2u * (uint32_t)level[order[r]] + (soon[order[r]] ? 0u : 1u);      // (fits: a level, a caller's too, is below 2^31)
 }
 
 // Packed neighbour rows of nodes v0 .. v0 + count - 1 in a fixed-width table: a node's row at its position (pos null:
