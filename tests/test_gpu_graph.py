@@ -53,6 +53,51 @@ def test_tables_match_the_oracle(name, n_and, hops, hint):
     assert np.array_equal(g.array("pair_order"), gh.array("pair_order"))
 
 
+def same_embeddings(n, g, host, hops):
+    """Level-by-level launches through the device tables of both graphs: a gate missing from the processing order, there twice
+    or in a wrong level leaves NaN rows or other bits."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    X = torch.randn(n, 128, generator=gen, device="cuda").to(torch.bfloat16)
+    W = [tuple((torch.randn(128, c, generator=gen, device="cuda") / 128 ** 0.5).to(torch.bfloat16) for c in (384, 128)) +
+         (torch.randn(4, 4, generator=gen, device="cuda"),)]
+    cfg = dg4.LayerConfig(128, 4, hops, 1, "bf16", per_level=True)
+    H = [torch.full_like(X, float("nan")) for _ in range(2)]
+    for h, graph in zip(H, (g, host)):
+        dg4.dg4_layer_fwd(cfg, graph, X, W, h)
+    assert not torch.isnan(H[0]).any()
+    assert torch.equal(*H)
+
+
+@pytest.mark.parametrize("n", [(1 << 20) - 1, (1 << 20) + 4_099])
+def test_sort_on_both_sides_of_two_to_the_twentieth(n):
+    # four and sixteen rounds of 256 items per workgroup, the last workgroup not full, up to three digits: the levels, and (three
+    # hops: no list schedule) the processing order
+    w = synth.make(synth.Config("million", 31, 4_100, n - 4_100, 9_000, 0.7, 260, 128, 4, 3, 1, "bf16"), features=False)
+    assert w.cfg.n_nodes == n
+    print(f"device graph build of {n} gates", flush=True)
+    edges = (w.edge_src, w.edge_dst, w.edge_inv)
+    g = build_on_gpu(n, *edges, 3)
+    same_as_oracle(g, oracle.build_levels(n, *edges, 3))
+    same_embeddings(n, g, dg4.dg4_build_levels(n, *edges, 3), 3)
+
+
+@pytest.mark.parametrize("n_and,cap,hops,deeper", [
+    (2_900, 3, 2, False), (8_200, 4, 2, False), (9_800, 4, 2, False),       # ordered on the host; from 24 n + entries = 2^18 on the GPU
+    (5_900, 0, 3, False), (7_900, 0, 3, False), (1_300, 0, 8, False), (6_500, 0, 5, False),
+    (30_000, 0, 2, False), (30_000, 5, 2, True),                            # beside a list schedule: on the host
+    (30_000, 5, 3, True),
+])
+def test_processing_order_made_on_the_host_or_on_the_gpu(n_and, cap, hops, deeper):
+    w = synth.make(synth.Config("order", 37, 300, n_and, 2_000, 0.8, cap, 128, 4, hops, 1, "bf16"), features=False)
+    n = w.cfg.n_nodes
+    edges = (w.edge_src, w.edge_dst, w.edge_inv)
+    host = dg4.dg4_build_levels(n, *edges, hops)
+    hint = np.ascontiguousarray(2 * host.array("level") + (host.array("level") > 0) * (np.arange(n) % 2), dtype=np.int32) if deeper else None
+    g = build_on_gpu(n, *edges, hops, hint)
+    print(f"order of {n} gates, {24 * n + g.nnz} against {1 << 18}, {n // host.n_levels} per level, hops {hops}, deeper {deeper}", flush=True)
+    same_embeddings(n, g, host, hops)
+
+
 def test_shuffled_edges_relabelled_nodes_and_not_nodes():
     w = synth.make("small", n_and=8000, features=False)
     n = w.cfg.n_nodes
