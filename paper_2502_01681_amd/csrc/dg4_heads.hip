@@ -260,8 +260,9 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
     // Neighbour rows: what is no source (padding, the gate itself) holds relation 0 and the row past the store's end. Narrow
     // rows of one layer lie there as the table has them: they are read once, and rewriting them is on every tile's way to its
     // sources (fp32 / 256, two hops, 30,300 gates: 3.242 -> 3.210 ms). Several layers read them several times (as the table has
-    // them: twelve layers fp32 / 128 5.88 -> 5.94 ms).
-    constexpr bool AS_STORED = W != 0 && ONE;
+    // them: twelve layers fp32 / 128 5.88 -> 5.94 ms; 8300 gates, four layers bf16 / 128 with feed-forward 1274 -> 1289 us), except
+    // in bf16 / 256 without feed-forward (four layers 1006 -> 988, three hops 1028 -> 1022, twelve 1381 -> 1375).
+    constexpr bool AS_STORED = W != 0 && (ONE || (sizeof(T) == 2 && D == 256 && !FFN));
     uint32_t* ent = (uint32_t*)(heads_smem + LDS::off_ent);
     const int tile_rows = W ? HR : p.tile_rows;
     const int ell_w = W ? W : LDS::row_words(p.ell_w, tile_rows);
