@@ -1098,6 +1098,11 @@ int launch_heads_t(const dg4_heads_args& a, int64_t groups, hipStream_t s)
     void (*kern)(dg4_heads_args) = nullptr;
     const auto pick = [&](auto w) -> void (*)(dg4_heads_args) {
         constexpr int W = decltype(w)::value;
+        // (one layer with feed-forward over narrow rows has a form of its own where that measured ahead: 19,500 gates, two hops, bf16 / 128
+        // 543 -> 535 us, fp32 / 128 718 -> 712, three hops, fp32 / 256 1619 -> 1499; but bf16 / 256 812 -> 820, fp32 / 256 over two
+        // hops 1472 -> 1476)
+        if constexpr (W != 0 && (D == 128 || (sizeof(T) == 4 && W == 16)))
+            if (a.ffn && a.n_layers == 1) return heads_kernel<T, D, W, true, true>;
         if (a.ffn) return heads_kernel<T, D, W, true, false>;
         return a.n_layers == 1 ? heads_kernel<T, D, W, false, true> : heads_kernel<T, D, W, false, false>;
     };

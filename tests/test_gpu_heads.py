@@ -35,11 +35,11 @@ def run(w, cfg, g, ffn=None, level_begin=0, level_end=None, H0=None):
     (3, 2, 1, 2, False),                    # fewer gates than a tile, fewer tiles than groups
     (700, 60, 2, 2, False), (700, 60, 3, 1, False),
     (2_500, 2_400, 2, 2, False),            # a hundred gates per level: tiles of two (hidden 128) and four
-    (600, 60, 2, 2, True),
+    (600, 60, 2, 2, True), (700, 60, 2, 1, True), (700, 60, 3, 1, True),
     (500, 20, 5, 2, False),                 # wide rows, tiles of two gates (16 lane groups and more per gate)
     (1_500, 900, 5, 1, False),              # ... of two
     (4_000, 3_900, 4, 2, False),            # ... of four (hidden 128) and eight
-    (900, 300, 6, 2, True),
+    (900, 300, 6, 2, True), (900, 300, 6, 1, True),
 ])
 def test_heads_kernel_against_oracle(hidden, dtype, n_and, window, hops, layers, ffn):
     print(f"heads kernel {dtype} {hidden} n_and={n_and} window={window} hops={hops} layers={layers} ffn={ffn}", flush=True)
