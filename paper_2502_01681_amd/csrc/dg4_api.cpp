@@ -690,7 +690,12 @@ extern "C" int dg4_layer_fwd(const dg4_layer_cfg* cfg, dg4_graph* g, const void*
             t.row_begin = p0; t.row_end = p1;
             // narrow rows, a level of few gates (bound by the latency of its launches): the attention
             // runs inside the output projection's launch. The same arithmetic either way, so the
-            // choice by the size of the level does not show in the result.
+            // choice by the size of the level does not show in the result. A sweep over 13 to 15 levels, this launch
+            // for all of them against two launches, us: bf16 / 128, two hops 237 and 264 at 2884 gates per level, 259 and 293 at
+            // 5769, 361 and 398 at 10,714, 980 and 1019 at 40,000; three hops 293 and 327, 427 and 448, 1230 and 1176 at the
+            // last three. fp32 / 128, two hops 355 and 382, 466 and 510, 736 and 797, 2195 and 2392; three hops 565 and 548, 936 and
+            // 863, 2953 and 2633 at the last three. So the line is right for three hops in fp32 / 128; the others would bear a
+            // higher one.
             const bool fuse_att = epi && g->ell_w <= 16 && p1 - p0 <= 4096;
             if (!fuse_att) HIPCHK(dg4_launch_attn(dt, d, t, s));
 
