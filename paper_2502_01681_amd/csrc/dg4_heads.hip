@@ -119,8 +119,12 @@ template <> struct Bits16<float> {
         d = fmaf(__uint_as_float(a.z), __uint_as_float(b.z), d);
         return fmaf(__uint_as_float(a.w), __uint_as_float(b.w), d);
     }
-    // eight lanes hold a head: the quads q and q + 2 of a row of 16 lanes
-    __device__ static __forceinline__ float head_sum(float p) { p += xor1(p); p += xor2(p); return quads_sum(p); }
+    // eight lanes hold a head: side by side, or (APART) the quads q and q + 2 of a row of 16 lanes
+    template <bool APART> __device__ static __forceinline__ float head_sum(float p)
+    {
+        p += xor1(p); p += xor2(p);
+        return APART ? quads_sum(p) : p + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(p), 0x141, 0xF, 0xF, true));
+    }
     __device__ static __forceinline__ float quads_sum(float p) { return p + ror<8>(p); }
 };
 template <> struct Bits16<bf16_t> {
@@ -144,7 +148,7 @@ template <> struct Bits16<bf16_t> {
         d0 = d2(a.z, b.z, d0); d1 = d2(a.w, b.w, d1);
         return d0 + d1;
     }
-    __device__ static __forceinline__ float head_sum(float p) { p += xor1(p); p += xor2(p); return p; }    // a quad holds a head
+    template <bool> __device__ static __forceinline__ float head_sum(float p) { p += xor1(p); p += xor2(p); return p; }    // a quad holds a head
     __device__ static __forceinline__ float quads_sum(float p) { return p; }
 };
 
@@ -261,8 +265,11 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
     // rows of one layer lie there as the table has them: they are read once, and rewriting them is on every tile's way to its
     // sources (fp32 / 256, two hops, 30,300 gates: 3.242 -> 3.210 ms). Several layers read them several times (as the table has
     // them: twelve layers fp32 / 128 5.88 -> 5.94 ms; 8300 gates, four layers bf16 / 128 with feed-forward 1274 -> 1289 us), except
-    // in bf16 / 256 without feed-forward (four layers 1006 -> 988, three hops 1028 -> 1022, twelve 1381 -> 1375).
-    constexpr bool AS_STORED = W != 0 && (ONE || (sizeof(T) == 2 && D == 256 && !FFN));
+    // in bf16 / 256 without feed-forward (four layers 1006 -> 988, three hops 1028 -> 1022, twelve 1381 -> 1375) and, together
+    // with lane groups of eight lanes side by side (alone it gains nothing), in fp32 / 128 with feed-forward over rows of 8
+    // entries (twelve layers, 9300 gates 5861 -> 5833, four 1768 -> 1764).
+    constexpr bool APART = sizeof(T) == 4 && !(W == 8 && FFN && D == 128);
+    constexpr bool AS_STORED = W != 0 && (ONE || (sizeof(T) == 2 && D == 256 && !FFN) || (sizeof(T) == 4 && !APART));
     uint32_t* ent = (uint32_t*)(heads_smem + LDS::off_ent);
     const int tile_rows = W ? HR : p.tile_rows;
     const int ell_w = W ? W : LDS::row_words(p.ell_w, tile_rows);
@@ -601,8 +608,8 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
                 *(uint4*)&qkv[n * QS + (wave / UH) * 32 + (wave % UH) * UC + g * CW] = Bits16<T>::pack(v);
             }
         };
-        // Attention roles: SG lane groups of LPS lanes share a gate (a group is a quad of lanes in bfloat16, the quads q
-        // and q + 2 of 16 lanes in fp32). Rows of 8 and 16 entries: group i takes the entries i, i + SG, ...; the K | V
+        // Attention roles: SG lane groups of LPS lanes share a gate (a group is a quad of lanes in bfloat16, in fp32 the quads q
+        // and q + 2 of 16 lanes). Rows of 8 and 16 entries: group i takes the entries i, i + SG, ...; the K | V
         // are requested a layer ahead (the sources are finished in every layer), so that from the second layer on
         // a narrow row waits for no memory. Wider rows: rounds of eight entries per group, dealt likewise.
         constexpr int SGN = HT / HR / LPS;        // (rows of 8 or 16 entries: tiles of 16)
@@ -613,9 +620,9 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
         auto gate_of = [&]() __attribute__((always_inline)) { return W ? tid / (HT / HR) : tid >> p.lanes_log2; };
         auto group_of = [&]() __attribute__((always_inline)) {
             const int t = tid & (lpg - 1);
-            return LPS == 4 ? t >> 2 : (t >> 4) * 2 + ((t >> 2) & 1);
+            return LPS == 4 ? t >> 2 : APART ? (t >> 4) * 2 + ((t >> 2) & 1) : t >> 3;
         };
-        auto sub_of = [&]() __attribute__((always_inline)) { return LPS == 4 ? tid & 3 : (tid & 3) | ((tid >> 1) & 4); };
+        auto sub_of = [&]() __attribute__((always_inline)) { return LPS == 4 ? tid & 3 : APART ? (tid & 3) | ((tid >> 1) & 4) : tid & 7; };
         auto piece = [&](const uint32_t* at) __attribute__((always_inline)) {
             const uint4 a = ((const uint4*)at)[0], b = ((const uint4*)at)[1];
             en[0] = a.x; en[1] = a.y; en[2] = a.z; en[3] = a.w;
@@ -699,7 +706,7 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
                     float m = -FLT_MAX, z = 0.f, av[E];
                     {                             // the gate itself (every row holds it), at its running state, in group 0
                         const bool own = r < rows && grp == 0;
-                        const float s = fmaf(Bits16<T>::head_sum(Bits16<T>::dot(q4, *(const uint4*)(qr + 32))), scale, bias[0]);
+                        const float s = fmaf(Bits16<T>::template head_sum<APART>(Bits16<T>::dot(q4, *(const uint4*)(qr + 32))), scale, bias[0]);
                         if (own) { m = fmaxf(s, -FLT_MAX); z = __expf(s - m); }
                         float v[E];
                         Bits16<T>::unpack(*(const uint4*)(qr + 64), v);
@@ -717,7 +724,7 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
 #pragma unroll
                             for (int j = 0; j < CH; ++j) {
                                 const uint32_t rel = en[j] >> 30;
-                                const float dot = Bits16<T>::head_sum(Bits16<T>::dot(q4, k4[j]));
+                                const float dot = Bits16<T>::template head_sum<APART>(Bits16<T>::dot(q4, k4[j]));
                                 const float bb = rel == 1 ? bias[1] : rel == 2 ? bias[2] : bias[3];
                                 sc[j] = is_source(en[j]) ? fmaf(dot, scale, bb) : -INFINITY;
                                 cm = fmaxf(cm, sc[j]);
@@ -794,14 +801,14 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
                     // the groups of a wave that share a gate, merged (all lanes take part)
                     float mm = m;
                     if (LPS == 4) mm = fmaxf(mm, ror<4>(mm));
-                    mm = fmaxf(mm, LPS == 4 ? ror<8>(mm) : xor4(mm));
+                    mm = fmaxf(mm, APART ? xor4(mm) : ror<8>(mm));
                     mm = max16(mm);
                     if (tile_rows <= 8) mm = max32(mm);
                     const float f = __expf(m - mm);
                     auto total_of = [&](float x) __attribute__((always_inline)) {
                         x *= f;
                         if (LPS == 4) x += ror<4>(x);
-                        x += LPS == 4 ? ror<8>(x) : xor4(x);
+                        x += APART ? xor4(x) : ror<8>(x);
                         x = add16(x);
                         return tile_rows <= 8 ? add32(x) : x;
                     };
