@@ -294,8 +294,10 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
     const int64_t N = p.n_rows;
     // One layer over wide rows asks for Wo behind the gathers (loads complete in order, and nothing but the gathers is in flight
     // then): with feed-forward, eight hops, 15,300 gates, bf16 / 128 841 -> 828 us, bf16 / 256 1267 -> 1249, fp32 / 256 2257 ->
-    // 2225. Not with feed-forward in fp32 / 128: 1074 -> 1082.
-    const bool wo_late = W == 0 && (ONE || (L == 1 && !(sizeof(T) == 4 && D == 128)));
+    // 2225. Not with feed-forward in fp32 / 128: 1074 -> 1082. With feed-forward a form of its own in bf16, because the choice at run
+    // time costs several layers (twelve over a partition, 15,300 gates: bf16 / 128 5773 -> 5800 us, bf16 / 256 9954 -> 10,032) but
+    // gains in fp32 / 256 (8300 gates 13,520 -> 13,290).
+    const bool wo_late = W == 0 && (ONE || (FFN && sizeof(T) == 4 && D == 256 && L == 1));
     uint32_t* flags = p.flags + (int64_t)slice * N;
 
     // phase timers (DG4_PROFILE): ticket, first projection + wait, attention + exchange, output projection + LayerNorm,
@@ -1105,10 +1107,10 @@ int launch_heads_t(const dg4_heads_args& a, int64_t groups, hipStream_t s)
     void (*kern)(dg4_heads_args) = nullptr;
     const auto pick = [&](auto w) -> void (*)(dg4_heads_args) {
         constexpr int W = decltype(w)::value;
-        // (one layer with feed-forward over narrow rows has a form of its own where that measured ahead: 19,500 gates, two hops, bf16 / 128
-        // 543 -> 535 us, fp32 / 128 718 -> 712, three hops, fp32 / 256 1619 -> 1499; but bf16 / 256 812 -> 820, fp32 / 256 over two
-        // hops 1472 -> 1476)
-        if constexpr (W != 0 && (D == 128 || (sizeof(T) == 4 && W == 16)))
+        // (one layer with feed-forward has a form of its own where that measured ahead: over narrow rows, 19,500 gates, two hops,
+        // bf16 / 128 543 -> 535 us, fp32 / 128 718 -> 712, three hops, fp32 / 256 1619 -> 1499; but bf16 / 256 812 -> 820, fp32 / 256
+        // over two hops 1472 -> 1476. Over wide rows in bf16, for the place of the request for Wo.)
+        if constexpr (W == 0 ? sizeof(T) == 2 : D == 128 || (sizeof(T) == 4 && W == 16))
             if (a.ffn && a.n_layers == 1) return heads_kernel<T, D, W, true, true>;
         if (a.ffn) return heads_kernel<T, D, W, true, false>;
         return a.n_layers == 1 ? heads_kernel<T, D, W, false, true> : heads_kernel<T, D, W, false, false>;
