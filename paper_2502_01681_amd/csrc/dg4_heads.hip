@@ -294,9 +294,9 @@ __global__ __launch_bounds__(HT) void heads_kernel(dg4_heads_args p)
     const int64_t N = p.n_rows;
     // One layer over wide rows asks for Wo behind the gathers (loads complete in order, and nothing but the gathers is in flight
     // then): with feed-forward, eight hops, 15,300 gates, bf16 / 128 841 -> 828 us, bf16 / 256 1267 -> 1249, fp32 / 256 2257 ->
-    // 2225. Not with feed-forward in fp32 / 128: 1074 -> 1082. With feed-forward a form of its own in bf16, because the choice at run
-    // time costs several layers (twelve over a partition, 15,300 gates: bf16 / 128 5773 -> 5800 us, bf16 / 256 9954 -> 10,032) but
-    // gains in fp32 / 256 (8300 gates 13,520 -> 13,290).
+    // 2225. Not with feed-forward in fp32 / 128 (1074 -> 1082), which takes the form for several layers. In that form a choice at run
+    // time is never taken; it costs twelve layers over a partition in bf16 (15,300 gates: hidden 128 5773 -> 5800 us, 256 9954 ->
+    // 10,032), but in fp32 / 256 it keeps the early request out of what is scheduled around it (8300 gates 13,520 -> 13,290).
     const bool wo_late = W == 0 && (ONE || (FFN && sizeof(T) == 4 && D == 256 && L == 1));
     uint32_t* flags = p.flags + (int64_t)slice * N;
 
@@ -1109,8 +1109,9 @@ int launch_heads_t(const dg4_heads_args& a, int64_t groups, hipStream_t s)
         constexpr int W = decltype(w)::value;
         // (one layer with feed-forward has a form of its own where that measured ahead: over narrow rows, 19,500 gates, two hops,
         // bf16 / 128 543 -> 535 us, fp32 / 128 718 -> 712, three hops, fp32 / 256 1619 -> 1499; but bf16 / 256 812 -> 820, fp32 / 256
-        // over two hops 1472 -> 1476. Over wide rows in bf16, for the place of the request for Wo.)
-        if constexpr (W == 0 ? sizeof(T) == 2 : D == 128 || (sizeof(T) == 4 && W == 16))
+        // over two hops 1472 -> 1476. Over wide rows where the request for Wo stands behind the gathers: fp32 / 256, five hops, 9300
+        // gates 1297 -> 1204.)
+        if constexpr (W == 0 ? !(sizeof(T) == 4 && D == 128) : D == 128 || (sizeof(T) == 4 && W == 16))
             if (a.ffn && a.n_layers == 1) return heads_kernel<T, D, W, true, true>;
         if (a.ffn) return heads_kernel<T, D, W, true, false>;
         return a.n_layers == 1 ? heads_kernel<T, D, W, false, true> : heads_kernel<T, D, W, false, false>;
